@@ -31,19 +31,36 @@ struct Radix {
 
 // Limbs [r*L, r*L + L) of the B-bit-limb form of (number at p >> bitoff),
 // where the number has nwords 32-bit words (zero beyond; zero when !live).
+// A lane's words come in vectors of four where all four are the number's: a
+// wave's numbers lie far apart, so a load costs the L1 a line per lane
+// whatever its width (one load per limb and word read 64 lines 2L times).
+// The words are then shifted so that limb k starts at bit B * k.
 template <int S, int G, int B>
 __device__ __forceinline__ void rload(uint32_t (&x)[S / G], const uint32_t *p, int nwords, int bitoff, bool live)
 {
-    constexpr int L = S / G;
-    const int r = grp_lane<G>();
+    constexpr int L = S / G, W = (B * L + 31) / 32 + 1, V = (W + 3) / 4;
+    const int pos = bitoff + B * L * (int)grp_lane<G>(), w0 = pos >> 5, sh = pos & 31;
+    uint32_t t[4 * V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int w = w0 + 4 * v;
+        if (live && w + 4 <= nwords) {
+            uint32_t q[4];
+            __builtin_memcpy(q, p + w, 16);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t[4 * v + j] = q[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) t[4 * v + j] = live && w + j < nwords ? p[w + j] : 0u;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j + 1 < W; ++j) t[j] = (uint32_t)((((uint64_t)t[j + 1] << 32) | t[j]) >> sh);
+    t[W - 1] >>= sh;
 #pragma unroll
     for (int k = 0; k < L; ++k) {
-        const int pos = bitoff + B * (r * L + k);
-        const int w = pos >> 5, sh = pos & 31;
-        const uint32_t lo = (live && w < nwords) ? p[w] : 0u;
-        const uint32_t hi = (live && w + 1 < nwords) ? p[w + 1] : 0u;
-        const uint64_t v = (((uint64_t)hi << 32) | lo) >> sh;
-        x[k] = (uint32_t)v & Radix<B>::MASK;
+        const int b = B * k, j = b >> 5, s = b & 31;
+        x[k] = (uint32_t)((((uint64_t)(j + 1 < 4 * V ? t[j + 1] : 0u) << 32) | t[j]) >> s) & Radix<B>::MASK;
     }
 }
 
@@ -157,17 +174,19 @@ __device__ __forceinline__ double grp_sum_f64(double v)
 }
 
 // (x + top * 2^(B*S)) / 2^e in double precision, for e near the value's bit
-// length (the top word is the group's top lane's; limbs far below 2^e
-// underflow harmlessly).
+// length (the top word is the group's top lane's; lanes far below 2^e
+// underflow harmlessly).  A lane's L limbs are one Horner chain, below
+// 2^(B*L + 1), scaled once.
 template <int S, int G, int B>
 __device__ __forceinline__ double rgrp_scaled(const uint32_t (&x)[S / G], uint32_t top, int e)
 {
     constexpr int L = S / G;
+    static_assert(B * (L + 1) < 1000, "a lane's limbs fit a double's exponent");
     const int r = grp_lane<G>();
-    double part = r == G - 1 ? ldexp((double)top, B * S - e) : 0.0;
+    double part = r == G - 1 ? (double)top : 0.0;
 #pragma unroll
-    for (int j = L - 1; j >= 0; --j) part += ldexp((double)x[j], B * (r * L + j) - e);
-    return grp_sum_f64<G>(part);
+    for (int j = L - 1; j >= 0; --j) part = fma(part, (double)(1u << B), (double)x[j]);
+    return grp_sum_f64<G>(ldexp(part, B * r * L - e));
 }
 
 // ---- accumulator normalisation -----------------------------------------
@@ -244,31 +263,20 @@ __device__ __forceinline__ void racc_lazy(uint32_t (&w)[S / G], const uint64_t (
     for (int j = 1; j < L; ++j) w[j] = ((uint32_t)v[j] & M) + h2[j - 1];
 }
 
-// x = x * 2^c mod n for canonical x < n, n < 2^(B*S - 10) and 1 <= c <= B - 1,
-// given rn = 2^bl / n in double precision (bl the bit length of n).  y =
-// x * 2^c is S limbs plus a top word (the bits beyond them, in the group's top
-// lane).  q = floor(y / n) - 2 .. floor(y / n) comes from the doubles y / 2^bl
-// and rn: their product is y / n within a relative 2^-45 and y / n < 2^c, so
-// it is off by less than one, and q is its floor lowered by one (never below
+// x = y mod n for y = x + top * 2^(B*S) (top: the group's top lane's) with
+// y / n < 2^(B-1), n < 2^(B*S - 2), given rn = 2^bl / n in double precision
+// (bl the bit length of n).  q = floor(y / n) - 1 or floor(y / n) comes from
+// the doubles y / 2^bl and rn: their product is y / n within a relative
+// 2^-45, 2^-17 in all, and q is the floor of that less 2^-16 (never below
 // zero), taken from the group's lane 0 so that every lane subtracts the same
-// q * n.  Then y - q * n < 3n fits S limbs, so it is the S-limb difference
-// modulo 2^(B*S), and at most two subtractions of n make it canonical.  One
-// call replaces c modular doublings (one carry chain each) by one multiply by
-// a limb and three carry chains.
+// q * n.  Then y - q * n < 2n fits S limbs, so it is the S-limb difference
+// modulo 2^(B*S), and at most one subtraction of n makes it canonical.
 template <int S, int G, int B>
-__device__ __forceinline__ void rgrp_shl_mod(uint32_t (&x)[S / G], uint32_t c, const uint32_t (&n)[S / G], double rn,
-                                             int bl)
+__device__ __forceinline__ void rgrp_sub_multiple(uint32_t (&x)[S / G], uint32_t top, const uint32_t (&n)[S / G],
+                                                  double rn, int bl)
 {
     constexpr int L = S / G;
-    constexpr uint32_t M = Radix<B>::MASK;
-    const uint32_t out = x[L - 1] >> (B - c);           // bits leaving this lane's top limb
-    const uint32_t in = grp_from_below<G>(out);
-    uint32_t y[L];
-#pragma unroll
-    for (int j = L - 1; j > 0; --j) y[j] = ((x[j] << c) & M) | (x[j - 1] >> (B - c));
-    y[0] = ((x[0] << c) & M) | in;
-    const uint32_t top = grp_lane<G>() == G - 1 ? out : 0u;
-    double qd = floor(rgrp_scaled<S, G, B>(y, top, bl) * rn) - 1.0;
+    double qd = floor(rgrp_scaled<S, G, B>(x, top, bl) * rn - 0x1p-16);
     qd = qd > 0.0 ? qd : 0.0;
     const uint32_t q = grp_bcast0<G>((uint32_t)qd);
     // q * n from 32-bit halves: a 64-bit product of the zero-extended limbs
@@ -279,9 +287,31 @@ __device__ __forceinline__ void rgrp_shl_mod(uint32_t (&x)[S / G], uint32_t c, c
     for (int j = 0; j < L; ++j) acc[j] = ((uint64_t)__umulhi(q, n[j]) << 32) | (uint32_t)(q * n[j]);
     uint32_t z[L];
     (void)racc_normalise<S, G, B>(z, acc);              // q * n modulo 2^(B*S)
+    uint32_t y[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) y[j] = x[j];
     (void)rgrp_sub<S, G, B>(x, y, z);                   // y - q * n, exact below 2^(B*S)
     rgrp_cond_sub<S, G, B>(x, 0u, n);
-    rgrp_cond_sub<S, G, B>(x, 0u, n);
+}
+
+// x = x * 2^c mod n for canonical x < n, n < 2^(B*S - 10) and 1 <= c <= B - 1,
+// given rn and bl as above: x * 2^c is S limbs plus a top word (the bits
+// beyond them, in the group's top lane), and its quotient by n is below 2^c.
+// One call replaces c modular doublings (one carry chain each) by one
+// multiply by a limb and three carry chains.
+template <int S, int G, int B>
+__device__ __forceinline__ void rgrp_shl_mod(uint32_t (&x)[S / G], uint32_t c, const uint32_t (&n)[S / G], double rn,
+                                             int bl)
+{
+    constexpr int L = S / G;
+    constexpr uint32_t M = Radix<B>::MASK;
+    const uint32_t out = x[L - 1] >> (B - c);           // bits leaving this lane's top limb
+    const uint32_t in = grp_from_below<G>(out);
+#pragma unroll
+    for (int j = L - 1; j > 0; --j) x[j] = ((x[j] << c) & M) | (x[j - 1] >> (B - c));
+    x[0] = ((x[0] << c) & M) | in;
+    const uint32_t top = grp_lane<G>() == G - 1 ? out : 0u;
+    rgrp_sub_multiple<S, G, B>(x, top, n, rn, bl);
 }
 
 // ---- Montgomery product, radix 2^B -----------------------------------------
