@@ -18,7 +18,9 @@
  *     asynchronous: the call returns before the results exist.  No entry
  *     point synchronises the device except rsa_device_errors.
  *   - Operands and the window table of each exponentiation live in
- *     registers and LDS.  No entry point allocates device memory per call:
+ *     registers and LDS.  Calls of several kernels pass intermediate integers
+ *     through the output words, which hold them until the call's work on the
+ *     stream is done.  No entry point allocates device memory per call:
  *     rsa_modexp_batch needs no scratch, rsa_ops_batch takes a caller
  *     workspace, and rsa_decrypt_crt_batch keeps one key-ordering buffer per
  *     device and stream handle, made the first time that stream needs one
@@ -91,10 +93,11 @@ int rsa_modexp_batch(const uint32_t *base, const uint32_t *exp, const uint32_t *
  * c must be < p*q (it is the caller's ciphertext).
  * Messages under the same key are processed together (one exponent per
  * wave): for more than one wave's worth of messages the call orders them by
- * a hash of their key words, each key's run starting a wave of its own where
- * the padding adds no round of waves to the launch, in a scratch buffer
- * (4 bytes per slot of that order, the batch rounded up to whole waves and
- * at most 2 waves per CU more, + 256 KiB) that the library keeps for the
+ * a hash of their key words, each key's run starting a wave (or a tile of 16
+ * messages) of its own where the padding adds no round of waves to the
+ * launch, in a scratch buffer (4 bytes per slot of that order, the batch
+ * rounded up to whole waves and at most 32 messages per SIMD more,
+ * + 256 KiB) that the library keeps for the
  * current device and this stream handle.  The first call on a stream, and a call with a larger
  * batch than that stream has seen, allocates it (hipMalloc; an outgrown
  * buffer is kept until the process ends, so graphs captured earlier stay
@@ -130,6 +133,14 @@ int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p, const uin
                                  uint32_t *out, size_t count, int limbs, hipStream_t stream);
 
 /*
+ * Exponentiations modulo 13 to 64 words (rsa_modexp_batch, and the halves of
+ * the plain CRT calls) run in a residue number system on the matrix cores
+ * where their width's plan is the default one, except where a batch is so
+ * large that the positional kernel is faster; exponents of at most 64 bits
+ * and every other width run on the positional kernels, which the plans below
+ * describe.  A plan that is not the default (rsa_set_plan) is obeyed for
+ * every exponentiation of its width.  Results do not depend on it.
+ *
  * Execution plan used for a limb width: the limb radix the kernel computes
  * in (radix_bits = 32, or 29 for the reduced-radix kernels whose 64-bit
  * accumulators need no carry handling), the kernel's limb count in that

@@ -12,6 +12,8 @@ import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
 
+from . import rns_tables
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
@@ -32,13 +34,19 @@ HIPCC_FLAGS = [
 ]
 
 
+# The RNS kernels hold constant matrices in accumulation registers and use the
+# products' accumulators on the vector unit: results in vector registers, and
+# a schedule for instruction-level parallelism (one wave per SIMD).
+RNS_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-sched-strategy=max-ilp"]
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
 def deps():
     return sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(CSRC, "*.def")) + \
-        [os.path.join(ROOT, "include", "rsagpu.h")]
+        [os.path.join(HERE, "rns_tables.py"), os.path.join(ROOT, "include", "rsagpu.h")]
 
 
 def peak_deps():
@@ -54,7 +62,8 @@ def hipcc() -> str:
 
 def _compile(src: str, extra) -> str:
     obj = os.path.join(OBJDIR, os.path.basename(src) + ".o")
-    cmd = [hipcc()] + HIPCC_FLAGS + list(extra) + ["-I", os.path.join(ROOT, "include"), "-c", src, "-o", obj]
+    flags = HIPCC_FLAGS + (RNS_FLAGS if os.path.basename(src).startswith("kern_rns_") else [])
+    cmd = [hipcc()] + flags + list(extra) + ["-I", os.path.join(ROOT, "include"), "-I", OBJDIR, "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
@@ -78,7 +87,7 @@ def _link(objs, out: str, verbose: bool) -> str:
 def build(verbose: bool = False, out: str = LIB, extra=(), jobs: int = 0) -> str:
     """Compile every HIP source and link librsagpu.so, and the multiply
     probe libmulpeak.so beside it (always recompiles)."""
-    os.makedirs(OBJDIR, exist_ok=True)
+    rns_tables.write(OBJDIR)
     srcs = sources() + [PEAK_SRC]
     jobs = jobs or min(16, os.cpu_count() or 1)
     with ThreadPoolExecutor(max_workers=jobs) as ex:

@@ -115,6 +115,35 @@ inline bool crt_lds_fits(int S, int G, int B, int w, int pairs)
 }
 
 
+// RNS exponentiation (rns_kernels.hpp): the launchers of one configuration.
+struct RnsCrtArgs {
+    const uint32_t *c, *p, *q, *dp, *dq, *qinv;
+    const unsigned *order;            // `slots` slots, or nullptr: the given order
+    uint32_t *out;
+    size_t count, slots;
+    int hl, cus;
+    unsigned long long *errs;
+};
+struct RnsExpArgs {
+    const uint32_t *base, *exp, *mod;
+    uint32_t *out;
+    size_t count;
+    int limbs, cus, window;
+    unsigned long long *errs;
+};
+typedef hipError_t (*rns_crt_launcher)(const RnsCrtArgs &, hipStream_t);
+typedef hipError_t (*rns_exp_launcher)(const RnsExpArgs &, hipStream_t);
+hipError_t rns_exp_u5(const RnsExpArgs &, hipStream_t);
+hipError_t rns_exp_u7(const RnsExpArgs &, hipStream_t);
+hipError_t rns_exp_u9(const RnsExpArgs &, hipStream_t);
+hipError_t rns_exp_u13(const RnsExpArgs &, hipStream_t);
+hipError_t rns_exp_u17(const RnsExpArgs &, hipStream_t);
+hipError_t rns_crt_u5(const RnsCrtArgs &, hipStream_t);
+hipError_t rns_crt_u7(const RnsCrtArgs &, hipStream_t);
+hipError_t rns_crt_u9(const RnsCrtArgs &, hipStream_t);
+hipError_t rns_crt_u13(const RnsCrtArgs &, hipStream_t);
+hipError_t rns_crt_u17(const RnsCrtArgs &, hipStream_t);
+
 template <int S, int G, int B>
 hipError_t launch_modexp(const uint32_t *base, const uint32_t *exp, const uint32_t *mod, uint32_t *out,
                          size_t count, int limbs, int w, unsigned long long *errs, hipStream_t stream);

@@ -153,6 +153,55 @@ const Instance *any_instance(int i, int B)
     return nullptr;
 }
 
+// RNS exponentiation (rns_kernels.hpp) of CRT halves, by width class; null
+// where there is none.  It takes the place of the positional kernel where the
+// class runs its default plan: a plan set by the caller names a positional
+// kernel and is obeyed.
+static const rns_crt_launcher kRnsCrt[] = {nullptr,     nullptr,     nullptr,      nullptr, &rns_crt_u5, &rns_crt_u7,
+                                           &rns_crt_u9, &rns_crt_u13, &rns_crt_u17, nullptr, nullptr};
+static_assert(sizeof(kRnsCrt) / sizeof(kRnsCrt[0]) == sizeof(kClasses) / sizeof(kClasses[0]), "one entry per class");
+
+static const rns_exp_launcher kRnsExp[] = {nullptr,     nullptr,     nullptr,      nullptr, &rns_exp_u5, &rns_exp_u7,
+                                           &rns_exp_u9, &rns_exp_u13, &rns_exp_u17, nullptr, nullptr};
+
+static bool default_plan(int kind, int i) { return g_plan[kind][i].load() == pack(kDefault[kind][i]); }
+
+static const size_t kRnsTile = 16;            // integers of one RNS tile
+
+// The RNS path of a plain CRT call, or nullptr.  For 512-bit halves it holds
+// one tile per SIMD: beyond that the positional kernel is the faster one (16
+// keys, 8000 messages: 439 us against 659; 32768: 1479 against 1303).
+static rns_crt_launcher rns_crt_of(int hl, size_t count, int cus)
+{
+    const int i = class_index(hl);
+    if (i < 0 || !default_plan(1, i)) return nullptr;
+    if (kClasses[i] <= 16 && 2 * ((count + kRnsTile - 1) / kRnsTile) > 4 * (size_t)cus) return nullptr;
+    return kRnsCrt[i];
+}
+
+// The RNS path of a plain exponentiation call, or nullptr.
+static rns_exp_launcher rns_exp_of(int limbs, size_t count, int cus)
+{
+    const int i = class_index(limbs);
+    if (i < 0 || !default_plan(0, i)) return nullptr;
+    const size_t tiles = (count + kRnsTile - 1) / kRnsTile;
+    if (kClasses[i] <= 16 && tiles > 4 * (size_t)cus) return nullptr;
+    if (kClasses[i] > 32 && tiles > (size_t)cus) return nullptr;
+    return kRnsExp[i];
+}
+
+// Slots of the processing order of an RNS call: the tiles of both halves may
+// grow to the next number at which their launch changes shape (one tile per
+// CU, two, or a multiple of four), so that each key's run can start a tile of
+// its own; never more than the padded runs can take.
+static size_t rns_order_slots(size_t count, int cus)
+{
+    const size_t cu = (size_t)cus, tiles = (count + kRnsTile - 1) / kRnsTile, both = 2 * tiles;
+    const size_t up = both <= cu ? cu : both <= 2 * cu ? 2 * cu : (both + 4 * cu - 1) / (4 * cu) * (4 * cu);
+    const size_t fit = up / 2 > tiles ? up / 2 : tiles, most = tiles + count;
+    return (fit < most ? fit : most) * kRnsTile;
+}
+
 static bool crt_kind(int kind) { return kind == 1 || kind == 3 || kind == 4; }
 
 bool resolve(int limbs, int kind, Resolved *r)
@@ -233,8 +282,11 @@ extern "C" int rsa_modexp_batch(const uint32_t *base, const uint32_t *exp, const
     if (!resolve(limbs, 0, &r)) return RSA_ELIMBS;
     if ((count + 64 / r.inst->G - 1) / (64 / r.inst->G) > 0x7FFFFFFFull) return RSA_EINVAL;
     unsigned long long *errs = nullptr;
-    const int st = device_state(&errs);
+    int cus = 1;
+    const int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
+    if (const rns_exp_launcher rns = rns_exp_of(limbs, count, cus))
+        return status_of(rns(RnsExpArgs{base, exp, mod, out, count, limbs, cus, r.w, errs}, stream));
     return status_of(r.inst->modexp(base, exp, mod, out, count, limbs, r.w, errs, stream));
 }
 
@@ -276,20 +328,23 @@ extern "C" int rsa_decrypt_crt_batch(const uint32_t *c, const uint32_t *p, const
     if (!c || !p || !q || !dp || !dq || !qinv || !out) return RSA_EINVAL;
     Resolved r;
     if (!resolve(limbs / 2, 1, &r)) return RSA_ELIMBS;
-    const size_t ng = 64 / r.inst->G;
-    if ((count + ng - 1) / ng > 0x7FFFFFFFull) return RSA_EINVAL;
+    if ((count + 64 / r.inst->G - 1) / (64 / r.inst->G) > 0x7FFFFFFFull) return RSA_EINVAL;
     unsigned long long *errs = nullptr;
     int cus = 1;
     const int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
+    const rns_crt_launcher rns = rns_crt_of(limbs / 2, count, cus);
+    const size_t ng = rns ? kRnsTile : 64 / r.inst->G;
     // more than one wave's worth of messages: process them grouped by key
     size_t slots = count;
     const unsigned *order = nullptr;
     if (count > ng) {
-        slots = key_order_slots(count, ng, (size_t)cus);
+        slots = rns ? rns_order_slots(count, cus) : key_order_slots(count, ng, (size_t)cus);
         order = key_order(p, dp, dq, count, limbs / 2, ng, slots, stream);
         if (!order) slots = count;
     }
+    if (rns)
+        return status_of(rns(RnsCrtArgs{c, p, q, dp, dq, qinv, order, out, count, slots, limbs / 2, cus, errs}, stream));
     return status_of(r.inst->crt(c, p, q, dp, dq, qinv, order, out, slots, limbs / 2, r.w,
                                  plain_crt_launch_pairs(r.inst, r.w, count, cus), errs, stream));
 }
@@ -306,18 +361,21 @@ extern "C" int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p
     if (count > RSA_CRT_STATIC_MAX_COUNT) return RSA_EINVAL;
     Resolved r;
     if (!resolve(limbs / 2, 1, &r)) return RSA_ELIMBS;
-    const size_t ng = 64 / r.inst->G;
     unsigned long long *errs = nullptr;
     int cus = 1;
     const int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
+    const rns_crt_launcher rns = rns_crt_of(limbs / 2, count, cus);
+    const size_t ng = rns ? kRnsTile : 64 / r.inst->G;
     size_t slots = count;
     const unsigned *order = nullptr;
     if (count > ng) {
-        const size_t want = key_order_slots(count, ng, (size_t)cus);
+        const size_t want = rns ? rns_order_slots(count, cus) : key_order_slots(count, ng, (size_t)cus);
         slots = want < kStaticOrderMax ? want : kStaticOrderMax;    // >= count
         if (!(order = key_order_static(p, dp, dq, count, limbs / 2, ng, slots, stream))) return RSA_EHIP;
     }
+    if (rns)
+        return status_of(rns(RnsCrtArgs{c, p, q, dp, dq, qinv, order, out, count, slots, limbs / 2, cus, errs}, stream));
     return status_of(r.inst->crt(c, p, q, dp, dq, qinv, order, out, slots, limbs / 2, r.w,
                                  plain_crt_launch_pairs(r.inst, r.w, count, cus), errs, stream));
 }
