@@ -173,6 +173,7 @@ struct rsa_keyset {
         int made;                       // streams (and their events) created so far
         hipStream_t streams[kStreams];
         hipEvent_t fork;
+        hipEvent_t entered;             // the widest bucket's way in is done (bulk batches)
         hipEvent_t done[kStreams];
     };
     ForkSet forksets[kForkSets];
@@ -275,6 +276,7 @@ extern "C" int rsa_keyset_destroy(rsa_keyset *ks)
             (void)hipEventDestroy(f.done[t]);
         }
         (void)hipEventDestroy(f.fork);
+        (void)hipEventDestroy(f.entered);
     }
     delete[] ks->info;
     delete ks;
@@ -308,6 +310,7 @@ extern "C" int rsa_keyset_add(rsa_keyset *ks, int limbs, const uint32_t *n, cons
     kd.cls = cls;
     kd.words = limbs;
     kd.hwords = h;
+    kd.rns = rns_coprime_host(hcls, p, h) && rns_coprime_host(hcls, q, h);
     uint32_t *cur = base;
     auto take = [&](size_t words) { uint32_t *r = cur; cur += words; return r; };
     uint32_t *dn = take(W), *de = take(W), *dpp = take(Hw), *dqq = take(Hw), *ddp = take(Hw), *ddq = take(Hw),
@@ -400,12 +403,22 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     // waves also raise their issue priority: every call ends with its
     // operations, whose chains are the longest, so on a SIMD shared with other
     // buckets' waves they issue first.
-    int order[kMaxBuckets], nb = 0;
-    for (int kind = 1; kind >= 0; --kind)
-        for (int cls = num_classes() - 1; cls >= 0; --cls)
-            if (mask & (1u << cls)) order[nb++] = cls * 2 + kind;
+    // In a bulk batch only the two widest fork, and the other CRT buckets follow
+    // the encryptions: a wide bucket's workgroups (nine or four waves) find no
+    // CU with room once one-wave tiles of a narrow bucket fill the SIMDs, so
+    // they get the encryptions' time as a start (mixed 32768-operation batch
+    // with three forks 7.2-7.7 ms, 4096-bit bucket ending last; with two %BULK%).
+    const bool bulk = nops >= kBulkOps;
+    int order[kMaxBuckets], nb = 0, crt[kMaxBuckets], ncrt = 0;
+    for (int cls = num_classes() - 1; cls >= 0; --cls)
+        if (mask & (1u << cls)) crt[ncrt++] = cls * 2 + 1;
+    const int first = bulk && ncrt > 2 ? 2 : ncrt;
+    for (int i = 0; i < first; ++i) order[nb++] = crt[i];
+    for (int i = 0; i < ncrt; ++i) order[nb++] = crt[i] - 1;
+    for (int i = first; i < ncrt; ++i) order[nb++] = crt[i];
     Resolved plan[kMaxBuckets];
     int pairs[kMaxBuckets];
+    rns_ops_launcher rns[kMaxBuckets];
     BucketUnits units;
     for (int b = 0; b < kMaxBuckets; ++b) units.u[b] = 1u;
     // rounded runs total at most nops + kKeySlots * 63 per bucket: kept 32-bit
@@ -414,13 +427,14 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
         const int b = order[t], cls = b / 2, kind = b % 2;
         const int width = kind == 0 ? class_width(cls) : class_width(cls) / 2;
         // the ops-batch plans; a bulk batch's widest CRT bucket, which ends it, its own
-        const int pkind = (kind == 1 && t == 0 && nops >= kBulkOps) ? 4 : kind + 2;
+        const int pkind = (kind == 1 && t == 0 && bulk) ? 4 : kind + 2;
         if (!resolve(width, pkind, &plan[t])) return RSA_ELIMBS;
         // the CRT buckets of a bulk batch: two pairs of waves per workgroup
         // where the LDS holds them (see crt_pairs)
         const Instance *in = plan[t].inst;
-        pairs[t] = kind == 1 && nops >= kBulkOps && crt_lds_fits(in->S, in->G, in->B, plan[t].w, 2) ? 2 : 1;
-        if (kind == 1 && round_runs) units.u[b] = (unsigned)(64 / plan[t].inst->G);
+        pairs[t] = kind == 1 && bulk && crt_lds_fits(in->S, in->G, in->B, plan[t].w, 2) ? 2 : 1;
+        rns[t] = kind == 1 ? rns_ops_of(width, pkind) : nullptr;
+        if (kind == 1 && round_runs) units.u[b] = rns[t] ? 16u : (unsigned)(64 / plan[t].inst->G);
     }
     const unsigned op_blocks = (unsigned)((nops + 255) / 256);
     const OpDesc *od = reinterpret_cast<const OpDesc *>(ops);
@@ -445,7 +459,7 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     // overlap the large ones.
     std::lock_guard<std::mutex> launch_lock(ks->launch_mu);
     rsa_keyset::ForkSet *fs = nullptr;
-    int nfork = ks->forks;
+    int nfork = bulk && ks->forks > 2 ? 2 : ks->forks;
     if (nfork > 0) {
         for (int i = 0; i < ks->nforksets; ++i)
             if (ks->forksets[i].caller == stream) fs = &ks->forksets[i];
@@ -460,6 +474,10 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
             f = rsa_keyset::ForkSet{};
             f.caller = stream;
             if (hipEventCreateWithFlags(&f.fork, hipEventDisableTiming) != hipSuccess) return RSA_EHIP;
+            if (hipEventCreateWithFlags(&f.entered, hipEventDisableTiming) != hipSuccess) {
+                (void)hipEventDestroy(f.fork);
+                return RSA_EHIP;
+            }
             fs = &ks->forksets[ks->nforksets++];
         }
         if (fs && !capturing) {
@@ -476,15 +494,31 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     }
     if (nfork > 0 && (e = hipEventRecord(fs->fork, stream)) != hipSuccess) return status_of(e);
     int forked = 0;
+    hipEvent_t lead = nullptr;          // recorded by the widest bucket of a bulk batch, see below
     for (int t = 0; t < nb; ++t) {
         const int b = order[t], kind = b % 2;
         const Resolved &r = plan[t];
-        int per = r.inst->blocks_per_cu(kind, r.w, pairs[t]);
-        if (per <= 0) per = 1;
-        const int blocks = per * cus;
         const bool fork = kind == 1 && t < nfork;
         hipStream_t s = fork ? fs->streams[t] : stream;
         if (fork && (e = hipStreamWaitEvent(s, fs->fork, 0)) != hipSuccess) return status_of(e);
+        if (rns[t]) {
+            // the bucket with its runs rounded up to whole tiles
+            const size_t padded = nops + (round_runs ? (size_t)kKeySlots * 15 : 0);
+            // a bulk batch's other buckets exponentiate only once the widest
+            // one's tiles can be placed
+            RnsOpsArgs a{ks->keys, od, lists + (size_t)b * cap, counts + b, in_pool, out_pool,
+                         padded < cap ? padded : cap, cus, bulk, nullptr, lead};
+            if (bulk && fork && t == 0) a.entered = lead = fs->entered;
+            if ((e = rns[t](a, s)) != hipSuccess) return status_of(e);
+            if (fork) {
+                if ((e = hipEventRecord(fs->done[t], s)) != hipSuccess) return status_of(e);
+                ++forked;
+            }
+            continue;
+        }
+        int per = r.inst->blocks_per_cu(kind, r.w, pairs[t]);
+        if (per <= 0) per = 1;
+        const int blocks = per * cus;
         const ops_launcher fn = kind == 0 ? r.inst->ops_enc : (pairs[t] > 1 ? r.inst->ops_crt_pairs : r.inst->ops_crt);
         e = fn(ks->keys, reinterpret_cast<const OpDesc *>(ops), lists + (size_t)b * cap, counts + b, counters + b,
                in_pool, out_pool, r.w, blocks, (kind == 1 && t == 0) ? 1 : 0, s);

@@ -131,8 +131,26 @@ struct RnsExpArgs {
     int limbs, cus, window;
     unsigned long long *errs;
 };
+struct RnsOpsArgs {
+    const KeyDev *keys;
+    const OpDesc *ops;
+    const unsigned *list, *size;      // the bucket (device)
+    const uint32_t *in_pool;
+    uint32_t *out_pool;
+    size_t most;                      // its size is at most this
+    int cus;
+    bool bulk;                        // of a bulk batch (kBulkOps)
+    hipEvent_t entered;               // if not null, recorded once the way in is done
+    hipEvent_t after;                 // if not null, waited for before the exponentiation
+};
+typedef hipError_t (*rns_ops_launcher)(const RnsOpsArgs &, hipStream_t);
 typedef hipError_t (*rns_crt_launcher)(const RnsCrtArgs &, hipStream_t);
 typedef hipError_t (*rns_exp_launcher)(const RnsExpArgs &, hipStream_t);
+hipError_t rns_ops_u5(const RnsOpsArgs &, hipStream_t);
+hipError_t rns_ops_u7(const RnsOpsArgs &, hipStream_t);
+hipError_t rns_ops_u9(const RnsOpsArgs &, hipStream_t);
+hipError_t rns_ops_u13(const RnsOpsArgs &, hipStream_t);
+hipError_t rns_ops_u17(const RnsOpsArgs &, hipStream_t);
 hipError_t rns_exp_u5(const RnsExpArgs &, hipStream_t);
 hipError_t rns_exp_u7(const RnsExpArgs &, hipStream_t);
 hipError_t rns_exp_u9(const RnsExpArgs &, hipStream_t);

@@ -35,6 +35,12 @@ struct Resolved {
     int w;
 };
 bool resolve(int limbs, int kind, Resolved *r);
+// RNS exponentiation of the CRT bucket whose halves have `hl` words at plan
+// `kind` (3 or 4), or nullptr; and whether a number of `words` words has no
+// factor in common with base A of the configuration of width class i (true
+// where there is none).
+rns_ops_launcher rns_ops_of(int hl, int kind);
+bool rns_coprime_host(int i, const uint32_t *n, int words);
 // rsa_ops_batch calls of at least this many operations take the kind-4 plan
 // for the CRT bucket of their widest class.
 static const size_t kBulkOps = 16384;

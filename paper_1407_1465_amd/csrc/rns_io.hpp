@@ -13,6 +13,7 @@
 // residue) and does not store.
 #pragma once
 
+#include "keyset_kernels.hpp"
 #include "modexp_kernels.hpp"
 #include "rns_arith.hpp"
 #include "rns_jobs.hpp"
@@ -198,8 +199,43 @@ __global__ __launch_bounds__(64 * kIoWaves) RSAGPU_EXP_OCC(S / G) void k_rns_ent
 
 // ---- leaving: Garner ----------------------------------------------------------
 //
-// m = m_q + q * (qinv * (m_p - m_q) mod p) from the halves k_rns_pow left in
-// the output, a wave over 64 / G messages; invalid elements give zero and are
+// m = m_q + q * (qinv * (m_p - m_q) mod p), from m_p, m_q, qinv * R mod p and
+// n = p, to `full` words at o (only when live; zeros when !valid).
+template <int S, int G>
+__device__ __forceinline__ void garner_store(uint32_t *o, uint32_t (&mp)[S / G], const uint32_t (&mq)[S / G],
+                                             const uint32_t (&qv)[S / G], const uint32_t (&n)[S / G],
+                                             const uint32_t (&qn)[S / G], uint32_t n0inv, int full, bool live,
+                                             bool valid, uint32_t *lds)
+{
+    using Ar = Arith<S, G, 29>;
+    using Ly = Layout<S, G>;
+    constexpr int L = S / G;
+    const int g = grp_index<G>(), r = grp_lane<G>();
+    uint32_t d[L], e[L], hh[L], high[L];
+    const uint32_t neg = Ar::sub(d, mp, mq);                     // m_p - m_q mod p  (m_q < q < p)
+#pragma unroll
+    for (int k = 0; k < L; ++k) e[k] = d[k];
+    Ar::add(e, n);
+#pragma unroll
+    for (int k = 0; k < L; ++k) d[k] = neg ? e[k] : d[k];
+    mont_mul_reg<S, G, 29>(hh, d, qv, lds, n, n0inv);
+    lds_sync();
+    lds_put<S, G>(lds, hh);
+    lds_sync();
+    uint32_t *stage = lds + Ly::WORDS + g * (2 * S);
+    auto sink = [&](int i, uint32_t v) {
+        if (r == 0) stage[i] = v;
+    };
+    Ar::mul_wide(high, mq, qn, lds, sink);
+#pragma unroll
+    for (int k = 0; k < L; ++k) stage[S + r * L + k] = high[k];
+    lds_sync();
+    if (live)
+        for (int wd = r; wd < full; wd += G) o[wd] = valid ? rword<29>(stage, 2 * S, wd) : 0u;
+}
+
+// The recombination of the halves k_rns_pow left in the
+// output, a wave over 64 / G messages; invalid elements give zero and are
 // counted.
 template <int S, int G>
 __global__ __launch_bounds__(64 * kIoWaves) void k_rns_leave_crt(const uint32_t *__restrict__ p, const uint32_t *__restrict__ q,
@@ -207,16 +243,14 @@ __global__ __launch_bounds__(64 * kIoWaves) void k_rns_leave_crt(const uint32_t 
                                                       unsigned long long count, int hl, unsigned long long *errs)
 {
     using Ar = Arith<S, G, 29>;
-    using Ly = Layout<S, G>;
     constexpr int L = S / G;
     uint32_t *lds = io_region<S, G>(2);
-    const int g = grp_index<G>(), r = grp_lane<G>();
-    const unsigned long long msg = io_first<G>() + g;
+    const int r = grp_lane<G>();
+    const unsigned long long msg = io_first<G>() + grp_index<G>();
     const bool live = msg < count;
     const size_t hoff = live ? (size_t)msg * (size_t)hl : 0, foff = 2 * hoff;
-    const int full = 2 * hl;
 
-    uint32_t n[L], qn[L], A[L], mq[L], qv[L], hh[L];
+    uint32_t n[L], qn[L], A[L], mq[L], qv[L];
     Ar::load(n, p + hoff, hl, 0, live);
     Ar::load(qn, q + hoff, hl, 0, live);
     Ar::load(mq, out + foff, hl, 0, live);
@@ -235,34 +269,101 @@ __global__ __launch_bounds__(64 * kIoWaves) void k_rns_leave_crt(const uint32_t 
     const uint32_t n0inv = Ar::n0inv(n0 | 1u);
     uint32_t one[L], r2[L];
     mont_setup<S, G, 29>(one, r2, n, n0inv, valid, lds);
-    {   // delta = m_p - m_q mod p  (m_q < q < p)
-        uint32_t d[L], e[L];
-        const uint32_t neg = Ar::sub(d, A, mq);
-#pragma unroll
-        for (int k = 0; k < L; ++k) e[k] = d[k];
-        Ar::add(e, n);
-#pragma unroll
-        for (int k = 0; k < L; ++k) A[k] = neg ? e[k] : d[k];
-    }
     mont_mul_reg<S, G, 29>(qv, qv, r2, lds, n, n0inv);          // qinv * R mod p
-    mont_mul_reg<S, G, 29>(hh, A, qv, lds, n, n0inv);           // delta * qinv mod p
-    lds_sync();
-    lds_put<S, G>(lds, hh);
-    lds_sync();
-    uint32_t *stage = lds + Ly::WORDS + g * (2 * S);
-    auto sink = [&](int i, uint32_t v) {
-        if (r == 0) stage[i] = v;
-    };
-    uint32_t high[L];
-    Ar::mul_wide(high, mq, qn, lds, sink);
-#pragma unroll
-    for (int k = 0; k < L; ++k) stage[S + r * L + k] = high[k];
-    lds_sync();
-    if (live) {
-        uint32_t *o = out + foff;
-        for (int wd = r; wd < full; wd += G) o[wd] = valid ? rword<29>(stage, 2 * S, wd) : 0u;
-    }
+    garner_store<S, G>(out + foff, A, mq, qv, n, qn, n0inv, 2 * hl, live, valid, lds);
     if (live && r == 0 && !valid) atomicAdd(errs, 1ull);
+}
+
+// ---- ops batches: CRT buckets under resident keys ---------------------------------
+//
+// The same two ways for a bucket's operations, with the keys' constants in
+// place of the set-up; workgroups take every gridDim.x-th run of the list.
+
+// c * A mod p and mod q, as k_rns_enter_crt; keys whose p or q has no inverse
+// for base A (KeyDev::rns) are exponentiated here.
+template <int S, int G, int U>
+__global__ __launch_bounds__(64 * kIoWaves) void k_rns_enter_ops(const KeyDev *__restrict__ keys,
+                                                                 const OpDesc *__restrict__ ops,
+                                                                 const unsigned *__restrict__ list,
+                                                                 const unsigned *__restrict__ size,
+                                                                 const uint32_t *in_pool, uint32_t *out_pool)
+{
+    using Ar = Arith<S, G, 29>;
+    constexpr int L = S / G, NG = 64 / G;
+    static_assert(standard_s29(S), "the limb count the keys' constants are stored with");
+    const int wave = (int)(threadIdx.x >> 6), half = wave & 1;
+    uint32_t *lds = io_region<S, G>(2);
+    const unsigned count = *size;
+#pragma unroll 1
+    for (unsigned first = blockIdx.x * (kIoWaves / 2) * NG; first < count; first += gridDim.x * (kIoWaves / 2) * NG) {
+        const unsigned idx = first + (wave >> 1) * NG + grp_index<G>();
+        const unsigned at = idx < count ? list[idx] : kOrderHole;
+        const bool live = at != kOrderHole;
+        const OpDesc &op = ops[live ? at : list[first]];         // the first entry of a run of tiles is no hole
+        const KeyDev &k = keys[op.key_id];
+        const int hl = k.hwords;
+        const ModConsts &mc = half ? k.cq[1] : k.cp[1];
+        uint32_t n[L], clo[L], chi[L], r2[L], r3[L], xt[L], x[L], t[L];
+        Ar::load(n, half ? k.q : k.p, hl, 0, live);
+        Ar::load(clo, in_pool + op.in_off, 2 * hl, 0, live);
+        Ar::load(chi, in_pool + op.in_off, 2 * hl, 29 * S, live);
+        load_raw<S, G>(r2, mc.r2, live);
+        load_raw<S, G>(r3, mc.r3, live);
+        const uint32_t n0inv = Ar::n0inv(grp_bcast0<G>(n[0]) | 1u);
+        mont_mul_reg<S, G, 29>(xt, clo, r2, lds, n, n0inv);      // c * R = c_lo * R + c_hi * R * R
+        mont_mul_reg<S, G, 29>(t, chi, r3, lds, n, n0inv);
+        {
+            const uint32_t ovf = Ar::add(xt, t);
+            Ar::cond_sub(xt, ovf, n);
+        }
+        rns_times_a<S, G, U>(x, xt, r2, n, n0inv, lds);
+        const bool rns = !live || k.rns;
+        if (__ballot(!rns)) {
+            uint32_t m[L], one[L];
+            load_raw<S, G>(one, mc.one, live);
+            group_modexp<S, G, 29>(m, xt, half ? k.dq : k.dp, hl, !rns, n, n0inv, one, lds, 2, xt);
+            from_mont<S, G, 29>(m, lds, n, n0inv);
+#pragma unroll
+            for (int i = 0; i < L; ++i) x[i] = rns ? x[i] : m[i];
+        }
+        __syncthreads();
+        store_words<S, G, 29>(out_pool + op.out_off + (half ? 0 : hl), x, hl, live, true, lds);
+        lds_sync();
+    }
+}
+
+// Garner, as k_rns_leave_crt.
+template <int S, int G>
+__global__ __launch_bounds__(64 * kIoWaves) void k_rns_leave_ops(const KeyDev *__restrict__ keys,
+                                                                 const OpDesc *__restrict__ ops,
+                                                                 const unsigned *__restrict__ list,
+                                                                 const unsigned *__restrict__ size, uint32_t *out_pool)
+{
+    using Ar = Arith<S, G, 29>;
+    constexpr int L = S / G, NG = 64 / G;
+    uint32_t *lds = io_region<S, G>(2);
+    const unsigned count = *size;
+#pragma unroll 1
+    for (unsigned first = (unsigned)io_first<G>(); first < count; first += gridDim.x * kIoWaves * NG) {
+        const unsigned idx = first + grp_index<G>();
+        const unsigned at = idx < count ? list[idx] : kOrderHole;
+        const bool live = at != kOrderHole;
+        const uint64_t any = __ballot(live);
+        if (any == 0) continue;
+        const OpDesc &op = ops[live ? at : list[first + (unsigned)__builtin_ctzll(any) / G]];
+        const KeyDev &k = keys[op.key_id];
+        const int hl = k.hwords;
+        uint32_t *o = out_pool + op.out_off;
+        uint32_t n[L], qn[L], A[L], mq[L], qv[L];
+        Ar::load(n, k.p, hl, 0, live);
+        Ar::load(qn, k.q, hl, 0, live);
+        Ar::load(mq, o, hl, 0, live);
+        Ar::load(A, o + hl, hl, 0, live);
+        load_raw<S, G>(qv, k.cp[1].xr, live);                    // qinv * R mod p
+        const uint32_t n0inv = Ar::n0inv(grp_bcast0<G>(n[0]) | 1u);
+        garner_store<S, G>(o, A, mq, qv, n, qn, n0inv, 2 * hl, live, true, lds);
+        lds_sync();
+    }
 }
 
 // ---- launchers ----------------------------------------------------------------
@@ -299,6 +400,29 @@ hipError_t launch_rns_exp_on(const RnsExpArgs &a, int window, hipStream_t stream
     if (e != hipSuccess) return e;
     const RnsExpSource<false> src{a.mod, a.exp, a.out, (unsigned long long)a.count, a.limbs};
     return rns_pow<U>(src, (a.count + 15) / 16, 1, a.cus, stream);
+}
+
+// A CRT bucket of an ops batch, at most `most` entries.
+template <int U, int S, int G>
+hipError_t launch_rns_ops(const RnsOpsArgs &a, hipStream_t stream)
+{
+    const size_t ng = 64 / G, lds = kIoWaves * lds_bytes_for(S, G, 29, 2);
+    const auto blocks = [&](size_t per) {
+        const size_t b = (a.most + per - 1) / per, cap = 2 * (size_t)a.cus;
+        return dim3((unsigned)(b < cap ? b : cap));
+    };
+    hipLaunchKernelGGL((k_rns_enter_ops<S, G, U>), blocks(ng * kIoWaves / 2), dim3(64 * kIoWaves), lds, stream, a.keys,
+                       a.ops, a.list, a.size, a.in_pool, a.out_pool);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (a.entered && (e = hipEventRecord(a.entered, stream)) != hipSuccess) return e;
+    if (a.after && (e = hipStreamWaitEvent(stream, a.after, 0)) != hipSuccess) return e;
+    const RnsOpsSource<false> src{a.keys, a.ops, a.list, a.size, a.out_pool, 0, 0};
+    e = rns_pow_bucket<U>(src, (a.most + 15) / 16, a.bulk, a.cus, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_rns_leave_ops<S, G>), blocks(ng * kIoWaves), dim3(64 * kIoWaves), lds, stream, a.keys, a.ops,
+                       a.list, a.size, a.out_pool);
+    return hipGetLastError();
 }
 
 // Narrow groups (S2 limbs on G2 lanes: a shorter chain of instructions per

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "launch.hpp"
+#include "keyset_types.hpp"
 
 namespace rsagpu {
 
@@ -104,11 +105,49 @@ struct RnsExpSource {
     }
 };
 
+// Jobs of one CRT bucket of an ops batch (its list and size are on the device);
+// blockIdx.y is the half.  The bucket is this launch's where its tiles number
+// above `above` and at most `upto` (launches of several shapes follow each
+// other, and the bucket's size picks one).
+template <bool LOOP>
+struct RnsOpsSource {
+    const KeyDev *keys;
+    const OpDesc *ops;
+    const unsigned *list, *size;
+    uint32_t *out_pool;
+    unsigned above, upto;
+    static constexpr bool kLoop = LOOP;
+    __device__ __forceinline__ unsigned long long tiles() const
+    {
+        const unsigned t = (*size + 15u) / 16u;
+        return t > above && t <= upto ? t : 0u;
+    }
+    __device__ __forceinline__ bool idle() const { return blockIdx.x >= tiles(); }
+    __device__ __forceinline__ RnsJob job(unsigned long long tile, int i) const
+    {
+        const unsigned first = (unsigned)tile * 16u, idx = first + (unsigned)i;
+        const unsigned at = idx < *size ? list[idx] : kOrderHole;
+        RnsJob j;
+        j.live = at != kOrderHole;
+        const OpDesc &op = ops[j.live ? at : list[first]];       // a tile's first entry is never a hole
+        const KeyDev &k = keys[op.key_id];
+        const bool second = blockIdx.y != 0;
+        j.n = second ? k.q : k.p;
+        j.e = second ? k.dq : k.dp;
+        j.words = k.hwords;
+        j.io = out_pool + op.out_off + (second ? 0 : k.hwords);
+        return j;
+    }
+};
+
 // k_rns_pow over `tiles` x `halves` tiles of a source, by configuration
 // (residues per lane and base); defined in kern_rns_u*.hip.
 template <int U>
 hipError_t rns_pow(const RnsCrtSource &src, size_t tiles, unsigned halves, int cus, hipStream_t stream);
 template <int U>
 hipError_t rns_pow(const RnsExpSource<false> &src, size_t tiles, unsigned halves, int cus, hipStream_t stream);
+// ... over a bucket of at most `tiles` tiles.
+template <int U>
+hipError_t rns_pow_bucket(const RnsOpsSource<false> &src, size_t tiles, bool bulk, int cus, hipStream_t stream);
 
 }  // namespace rsagpu

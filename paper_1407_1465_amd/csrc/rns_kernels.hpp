@@ -152,8 +152,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
     bool uniform;
     {
         bool same = true;
-        for (int k = 0; k < job.words; ++k) {
-            const uint32_t ev = job.e[k];
+        const int most = (int)wave_max((uint32_t)job.words);     // (an ops bucket's keys may differ in words)
+        for (int k = 0; k < most; ++k) {
+            const uint32_t ev = k < job.words ? job.e[k] : 0u;
             if (ev) ebits = 32 * k + 32 - __clz(ev);
             same = same && ev == (uint32_t)__builtin_amdgcn_readfirstlane((int)ev);
         }
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
         }
     }
     if (uniform) {
-        eb = ExpBits{first_lane_ptr(job.e), job.words, 0, 0, 0};
+        eb = ExpBits{first_lane_ptr(job.e), __builtin_amdgcn_readfirstlane(job.words), 0, 0, 0};
         pos = __builtin_amdgcn_readfirstlane(ebits) - 1;
         if (pos >= 0) {
             eb.start(pos);
@@ -384,8 +385,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
     uint32_t *op = reinterpret_cast<uint32_t *>(from(job.io));
     const bool live = __shfl((int)job.live, gi) != 0 && (int)grp_index<G>() < 16 && nostore[gi] == 0u;
     const bool unit = __shfl((int)zero_exp, gi) != 0;
+    const int words = __shfl(job.words, gi);
     uint32_t n[L], x[L];
-    Ar::load(n, np, job.words, 0, true);
+    Ar::load(n, np, words, 0, true);
     {
         uint64_t acc[L], hi[L];
 #pragma unroll
@@ -422,7 +424,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
 #pragma unroll
         for (int k = 0; k < L; ++k) x[k] = r == 0 && k == 0 ? 1u : 0u;
     }
-    store_words<S, G, 29>(op, x, job.words, live, true, pos_buf);
+    store_words<S, G, 29>(op, x, words, live, true, pos_buf);
     lds_sync();
     } while (Source::kLoop && tile < src.tiles());
 }
@@ -477,10 +479,50 @@ hipError_t launch_rns_tiles(const Source &src, size_t tiles, unsigned halves, in
         return launch_rns_pow<U, 4, 2>(src, grid, 4, stream);
     } else {
         static_assert(U == 17, "a configuration of rns_tables.py");
-        if (all <= cu) return launch_rns_pow<U, 9, 2>(src, grid, 4, stream);
-        if constexpr (Source::kExp) return launch_rns_pow<U, 6, 2>(src.looping(), resident(1), 4, stream);
-        return launch_rns_pow<U, 6, 2>(src, grid, 4, stream);
+        return launch_rns_pow<U, 9, 2>(src, grid, 4, stream);
     }
+}
+
+// The halves of an ops batch's CRT bucket, whose size only the device knows.  A
+// bulk batch takes the shape for many tiles, whatever a bucket holds.  For a
+// smaller batch both shapes are launched, and the bucket's size decides which
+// one's workgroups end at once (beside other buckets' waves even those wait
+// for a CU with room: in a bulk batch the empty launches of nine-wave
+// workgroups held the 2048-bit bucket back by 3 ms).
+template <int U>
+hipError_t launch_rns_bucket(const RnsOpsSource<false> &src, size_t tiles, bool bulk, int cus, hipStream_t stream)
+{
+    const unsigned cu = (unsigned)(cus > 0 ? cus : 1), few = bulk ? 0 : cu / 2;
+    RnsOpsSource<false> lo = src;
+    lo.above = 0;
+    lo.upto = few;
+    const RnsOpsSource<true> hi{src.keys, src.ops, src.list, src.size, src.out_pool, few, ~0u};
+    const dim3 glo((unsigned)(tiles < few ? tiles : few), 2);
+    const auto ghi = [&](unsigned per_cu) {
+        const unsigned most = per_cu * cu / 2;
+        return dim3(tiles < most ? (unsigned)tiles : most, 2);
+    };
+    hipError_t e = hipSuccess;
+    if constexpr (U == 5) {
+        RnsOpsSource<true> all = hi;
+        all.above = 0;
+        return launch_rns_pow<U, 1, 1>(all, ghi(4), 4, stream);
+    } else if constexpr (U == 7) {
+        if (!bulk) e = launch_rns_pow<U, 7, 4>(lo, glo, 4, stream);
+        if (e == hipSuccess && tiles > few) e = launch_rns_pow<U, 1, 1>(hi, ghi(4), 4, stream);
+    } else if constexpr (U == 9) {
+        if (!bulk) e = launch_rns_pow<U, 9, 4>(lo, glo, 5, stream);
+        if (e == hipSuccess && tiles > few) e = launch_rns_pow<U, 1, 1>(hi, ghi(4), 4, stream);
+    } else if constexpr (U == 13) {
+        if (!bulk) e = launch_rns_pow<U, 13, 4>(lo, glo, 5, stream);
+        if (e == hipSuccess && tiles > few) e = launch_rns_pow<U, 4, 2>(hi, ghi(2), 4, stream);
+    } else {
+        RnsOpsSource<false> all = src;
+        all.above = 0;
+        all.upto = ~0u;
+        return launch_rns_pow<U, 9, 2>(all, dim3((unsigned)tiles, 2), 4, stream);
+    }
+    return e;
 }
 
 #define RSAGPU_INSTANTIATE_RNS(U_)                                                                              \
@@ -493,6 +535,12 @@ hipError_t launch_rns_tiles(const Source &src, size_t tiles, unsigned halves, in
     hipError_t rns_pow<U_>(const RnsExpSource<false> &src, size_t tiles, unsigned halves, int cus, hipStream_t stream) \
     {                                                                                                           \
         return launch_rns_tiles<U_>(src, tiles, halves, cus, stream);                                           \
+    }                                                                                                           \
+    template <>                                                                                                 \
+    hipError_t rns_pow_bucket<U_>(const RnsOpsSource<false> &src, size_t tiles, bool bulk, int cus,             \
+                                  hipStream_t stream)                                                           \
+    {                                                                                                           \
+        return launch_rns_bucket<U_>(src, tiles, bulk, cus, stream);                                            \
     }
 
 }  // namespace rsagpu

@@ -166,6 +166,44 @@ static const rns_exp_launcher kRnsExp[] = {nullptr,     nullptr,     nullptr,   
 
 static bool default_plan(int kind, int i) { return g_plan[kind][i].load() == pack(kDefault[kind][i]); }
 
+static const rns_ops_launcher kRnsOps[] = {nullptr,     nullptr,     nullptr,      nullptr, &rns_ops_u5, &rns_ops_u7,
+                                           &rns_ops_u9, &rns_ops_u13, &rns_ops_u17, nullptr, nullptr};
+
+rns_ops_launcher rns_ops_of(int hl, int kind)
+{
+    std::call_once(g_plan_once, init_plans);
+    const int i = class_index(hl);
+    return i >= 0 && default_plan(kind, i) ? kRnsOps[i] : nullptr;
+}
+
+#include "rns_primes.inc"
+
+bool rns_coprime_host(int i, const uint32_t *n, int words)
+{
+    const uint32_t *primes = nullptr;
+    int count = 0;
+    switch (kClasses[i]) {
+#define RNS_CLASS(W_, U_)                                     \
+    case W_:                                                  \
+        primes = kRnsPrimes##U_;                              \
+        count = sizeof(kRnsPrimes##U_) / sizeof(uint32_t);    \
+        break;
+        RNS_CLASS(16, 5)
+        RNS_CLASS(24, 7)
+        RNS_CLASS(32, 9)
+        RNS_CLASS(48, 13)
+        RNS_CLASS(64, 17)
+#undef RNS_CLASS
+    default: break;
+    }
+    for (int k = 0; k < count; ++k) {
+        uint64_t r = 0;
+        for (int w = words - 1; w >= 0; --w) r = (r << 32 | n[w]) % primes[k];
+        if (r == 0) return false;
+    }
+    return true;
+}
+
 static const size_t kRnsTile = 16;            // integers of one RNS tile
 
 // The RNS path of a plain CRT call, or nullptr.  For 512-bit halves it holds

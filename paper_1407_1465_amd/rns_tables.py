@@ -202,12 +202,23 @@ def source(units: int, limbs: int, bits: int) -> str:
     return "".join(out)
 
 
+def primes_source() -> str:
+    """C++ source of every configuration's base A, for host code."""
+    out = ["// Generated by rns_tables.py; do not edit.\n"]
+    for units, limbs, bits in CONFIGS:
+        a = Config(units, limbs, bits).a
+        out.append("static const uint32_t kRnsPrimes%d[%d] = {%s};\n" % (units, len(a), ", ".join("%du" % p for p in a)))
+    return "".join(out)
+
+
 def write(directory: str) -> None:
-    """Writes rns_tables_<units>.inc for every configuration."""
+    """Writes rns_tables_<units>.inc for every configuration, and
+    rns_primes.inc."""
     os.makedirs(directory, exist_ok=True)
-    for cfg in CONFIGS:
-        path = os.path.join(directory, "rns_tables_%d.inc" % cfg[0])
-        text = source(*cfg)
+    files = {"rns_tables_%d.inc" % cfg[0]: source(*cfg) for cfg in CONFIGS}
+    files["rns_primes.inc"] = primes_source()
+    for name, text in files.items():
+        path = os.path.join(directory, name)
         if os.path.exists(path) and open(path).read() == text:
             continue
         tmp = path + ".tmp%d" % os.getpid()
