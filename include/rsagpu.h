@@ -134,10 +134,11 @@ int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p, const uin
 
 /*
  * Exponentiations modulo 13 to 64 words (rsa_modexp_batch, and the halves of
- * the plain CRT calls) run in a residue number system on the matrix cores
+ * CRT decryptions, also in rsa_ops_batch) run in a residue number system on
+ * the matrix cores
  * where their width's plan is the default one, except where a batch is so
- * large that the positional kernel is faster; exponents of at most 64 bits
- * and every other width run on the positional kernels, which the plans below
+ * large that the positional kernel is faster; exponents of at most 64 bits,
+ * encryptions and every other width run on the positional kernels, which the plans below
  * describe.  A plan that is not the default (rsa_set_plan) is obeyed for
  * every exponentiation of its width.  Results do not depend on it.
  *
@@ -272,7 +273,8 @@ int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, const uint32_t
 /*
  * Streams an rsa_ops_batch call forks its widest CRT buckets onto (0 to 3,
  * default 3), beside the caller's stream, which runs every other bucket and
- * then waits for the forks.  Each caller stream has a fork set of its own
+ * then waits for the forks; calls of at least 16384 operations use at most
+ * two.  Each caller stream has a fork set of its own
  * (up to 8 caller streams per keyset; further callers, and a caller first
  * seen while it is being captured into a graph, run unforked), so calls on
  * different caller streams overlap on the device.  A process has 4 hardware

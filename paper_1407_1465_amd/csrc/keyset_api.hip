@@ -173,7 +173,6 @@ struct rsa_keyset {
         int made;                       // streams (and their events) created so far
         hipStream_t streams[kStreams];
         hipEvent_t fork;
-        hipEvent_t entered;             // the widest bucket's way in is done (bulk batches)
         hipEvent_t done[kStreams];
     };
     ForkSet forksets[kForkSets];
@@ -276,7 +275,6 @@ extern "C" int rsa_keyset_destroy(rsa_keyset *ks)
             (void)hipEventDestroy(f.done[t]);
         }
         (void)hipEventDestroy(f.fork);
-        (void)hipEventDestroy(f.entered);
     }
     delete[] ks->info;
     delete ks;
@@ -407,7 +405,7 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     // the encryptions: a wide bucket's workgroups (nine or four waves) find no
     // CU with room once one-wave tiles of a narrow bucket fill the SIMDs, so
     // they get the encryptions' time as a start (mixed 32768-operation batch
-    // with three forks 7.2-7.7 ms, 4096-bit bucket ending last; with two %BULK%).
+    // with three forks and the encryptions last 7.65 ms, now 7.2 ms).
     const bool bulk = nops >= kBulkOps;
     int order[kMaxBuckets], nb = 0, crt[kMaxBuckets], ncrt = 0;
     for (int cls = num_classes() - 1; cls >= 0; --cls)
@@ -474,10 +472,6 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
             f = rsa_keyset::ForkSet{};
             f.caller = stream;
             if (hipEventCreateWithFlags(&f.fork, hipEventDisableTiming) != hipSuccess) return RSA_EHIP;
-            if (hipEventCreateWithFlags(&f.entered, hipEventDisableTiming) != hipSuccess) {
-                (void)hipEventDestroy(f.fork);
-                return RSA_EHIP;
-            }
             fs = &ks->forksets[ks->nforksets++];
         }
         if (fs && !capturing) {
@@ -494,7 +488,6 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     }
     if (nfork > 0 && (e = hipEventRecord(fs->fork, stream)) != hipSuccess) return status_of(e);
     int forked = 0;
-    hipEvent_t lead = nullptr;          // recorded by the widest bucket of a bulk batch, see below
     for (int t = 0; t < nb; ++t) {
         const int b = order[t], kind = b % 2;
         const Resolved &r = plan[t];
@@ -504,11 +497,8 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
         if (rns[t]) {
             // the bucket with its runs rounded up to whole tiles
             const size_t padded = nops + (round_runs ? (size_t)kKeySlots * 15 : 0);
-            // a bulk batch's other buckets exponentiate only once the widest
-            // one's tiles can be placed
-            RnsOpsArgs a{ks->keys, od, lists + (size_t)b * cap, counts + b, in_pool, out_pool,
-                         padded < cap ? padded : cap, cus, bulk, nullptr, lead};
-            if (bulk && fork && t == 0) a.entered = lead = fs->entered;
+            const RnsOpsArgs a{ks->keys, od, lists + (size_t)b * cap, counts + b, in_pool, out_pool,
+                               padded < cap ? padded : cap, cus, bulk};
             if ((e = rns[t](a, s)) != hipSuccess) return status_of(e);
             if (fork) {
                 if ((e = hipEventRecord(fs->done[t], s)) != hipSuccess) return status_of(e);

@@ -140,8 +140,6 @@ struct RnsOpsArgs {
     size_t most;                      // its size is at most this
     int cus;
     bool bulk;                        // of a bulk batch (kBulkOps)
-    hipEvent_t entered;               // if not null, recorded once the way in is done
-    hipEvent_t after;                 // if not null, waited for before the exponentiation
 };
 typedef hipError_t (*rns_ops_launcher)(const RnsOpsArgs &, hipStream_t);
 typedef hipError_t (*rns_crt_launcher)(const RnsCrtArgs &, hipStream_t);

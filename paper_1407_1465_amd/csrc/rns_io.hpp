@@ -415,8 +415,6 @@ hipError_t launch_rns_ops(const RnsOpsArgs &a, hipStream_t stream)
                        a.ops, a.list, a.size, a.in_pool, a.out_pool);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.entered && (e = hipEventRecord(a.entered, stream)) != hipSuccess) return e;
-    if (a.after && (e = hipStreamWaitEvent(stream, a.after, 0)) != hipSuccess) return e;
     const RnsOpsSource<false> src{a.keys, a.ops, a.list, a.size, a.out_pool, 0, 0};
     e = rns_pow_bucket<U>(src, (a.most + 15) / 16, a.bulk, a.cus, stream);
     if (e != hipSuccess) return e;

@@ -131,6 +131,7 @@ struct RnsOpsSource {
         j.live = at != kOrderHole;
         const OpDesc &op = ops[j.live ? at : list[first]];       // a tile's first entry is never a hole
         const KeyDev &k = keys[op.key_id];
+        j.live = j.live && k.rns != 0;                           // (k_rns_enter_ops has done the others)
         const bool second = blockIdx.y != 0;
         j.n = second ? k.q : k.p;
         j.e = second ? k.dq : k.dp;

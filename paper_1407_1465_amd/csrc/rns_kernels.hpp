@@ -451,7 +451,8 @@ hipError_t launch_rns_pow(const Source &src, dim3 grid, int w, hipStream_t strea
 // and 3402 with 3 waves.  3072-bit keys, 777 messages (114 tiles) 1467 with
 // 13 waves, 1580 with 7, 1779 with 5; 4096 messages 2280 with 4 and 3078
 // with 7.  4096-bit keys, 1092 messages 2582 with 9 waves, 2772 with 6, 3049
-// with 4; 4368 messages 8252 with 6 and 8892 with 4.
+// with 4; 4368 messages 7732 with 9, 8252 with 6 and 8892 with 4.  The window
+// is the widest whose table leaves LDS for the workgroups a CU is to hold.
 template <int U, typename Source>
 hipError_t launch_rns_tiles(const Source &src, size_t tiles, unsigned halves, int cus, hipStream_t stream)
 {
@@ -479,7 +480,7 @@ hipError_t launch_rns_tiles(const Source &src, size_t tiles, unsigned halves, in
         return launch_rns_pow<U, 4, 2>(src, grid, 4, stream);
     } else {
         static_assert(U == 17, "a configuration of rns_tables.py");
-        return launch_rns_pow<U, 9, 2>(src, grid, 4, stream);
+        return launch_rns_pow<U, 9, 2>(src, grid, 5, stream);
     }
 }
 
@@ -520,7 +521,7 @@ hipError_t launch_rns_bucket(const RnsOpsSource<false> &src, size_t tiles, bool 
         RnsOpsSource<false> all = src;
         all.above = 0;
         all.upto = ~0u;
-        return launch_rns_pow<U, 9, 2>(all, dim3((unsigned)tiles, 2), 4, stream);
+        return launch_rns_pow<U, 9, 2>(all, dim3((unsigned)tiles, 2), 5, stream);
     }
     return e;
 }

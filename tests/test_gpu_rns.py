@@ -130,3 +130,55 @@ def test_crt_launch_shapes(limbs, count):
     assert rsagpu.device_errors() == 2
     check(rsagpu.decrypt_crt(cd, *ops, out=cd), want, limbs)
     assert rsagpu.device_errors() == 2
+
+
+# buckets of a few tiles, of more tiles than half the CUs, and of a bulk batch
+@pytest.mark.parametrize("per_class,inplace", [(20, True), (2200, False), (4000, True)])
+def test_ops_buckets(per_class, inplace):
+    """CRT decryptions under resident keys whose primes are any odd numbers: of
+    every RNS class, some narrower than their class, some sharing a factor with
+    base A, small runs that leave tiles with empty slots; in place and not."""
+    rng = random.Random(per_class)
+    ks, keys = rsagpu.KeySet(32), []
+    for h in (13, 16, 24, 29, 32, 48, 64):
+        words, bits = min(w for w in CLASSES if w >= h), 32 * h
+        for j in range(3):
+            while True:
+                p, q = odd(rng, bits), odd(rng, bits)
+                if j == 1:
+                    q = base_multiple(rng, words, bits - 2)
+                p, q = max(p, q), min(p, q)
+                if math.gcd(p, q) == 1 and p != q:
+                    break
+            key = (p, q, rng.getrandbits(70), rng.getrandbits(90), pow(q, -1, p))
+            keys.append((2 * h, key))
+            assert ks.add(2 * h, p * q, 65537, *key) == len(keys) - 1
+    kids = [k for j in range(0, len(keys), 3) for k in
+            [j] * (per_class - 3) + [j + 1] * 2 + [j + 2]][:]
+    rng.shuffle(kids)
+    ins, want, offs, kinds = [], [], [], []
+    at = 0
+    for k in kids:
+        limbs, (p, q, dp, dq, qinv) = keys[k]
+        v = rng.randrange(p * q)
+        enc = rng.random() < 0.1
+        if enc:
+            r = pow(v, 65537, p * q)
+        else:
+            mp, mq = pow(v, dp, p), pow(v, dq, q)
+            r = mq + q * ((mp - mq) * qinv % p)
+        ins.append(W.int_to_limbs(v, limbs))
+        want.append(W.int_to_limbs(r, limbs))
+        offs.append(at)
+        kinds.append(0 if enc else 1)
+        at += limbs
+    pool = dev(np.concatenate(ins))
+    out = pool if inplace else torch.zeros_like(pool)
+    ops = rsagpu.pack_ops(kinds, kids, offs, offs).cuda()
+    ws = torch.empty(rsagpu.ops_workspace_size(len(kids)), dtype=torch.uint8, device="cuda")
+    rsagpu.device_errors()
+    rsagpu.ops_batch(ks, ops, pool, out, ws)
+    got = host(out)
+    bad = [i for i, (o, w) in enumerate(zip(offs, want)) if not np.array_equal(got[o:o + len(w)], w)]
+    assert not bad, "%d of %d differ, first %d (key %d)" % (len(bad), len(kids), bad[0], kids[bad[0]])
+    assert rsagpu.device_errors() == 0
