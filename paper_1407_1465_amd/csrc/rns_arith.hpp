@@ -12,11 +12,11 @@
 // wave runs it for its 16 integers at once on the matrix cores: residues as
 // four signed base-256 digits, the matrix's entries likewise, exact 32-bit
 // accumulators.  What is left for the vector unit grows with k, not with
-// k^2 (27 instructions per residue pair and product; the positional product
+// k^2 (25 instructions per residue pair and product; the positional product
 // of radix_bn.hpp grows with the square of the width).
 //
-// Values are bounded, never reduced: residues are signed 32-bit words, with
-// |xi| <= 0.73 m.  q carries a multiple of A (its extension is not
+// Values are bounded, never reduced: residues are signed 32-bit words below
+// 0.9 * 2^31 (those in A below 0.73 m).  q carries a multiple of A (its extension is not
 // corrected), so |r| <= |x y| / A + 0.73 k n < 0.75 k n for inputs of that
 // size (rns_tables.py checks A and B against it).  The extension back is
 // exact: alpha = round(sum_j xi_j / b_j) comes from the sum of the residues'
@@ -28,6 +28,10 @@
 // Word products reduce by Montgomery's method with 2^32 and signed words:
 // for |t| < 2^63 and u = -t / m mod 2^32 as a signed word, (t + u m) / 2^32
 // is below |t| / 2^32 + m / 2.
+//
+// In B the new residue is red(s kappa + q v) with s = red(x y) and v from n;
+// the extended q is a 47-bit sum lo + 2^16 hi of accumulators, and enters as
+// lo v + hi v16 with v16 = 2^16 v mod b_j: no reduction of its own.
 //
 // Layout: lane l holds the residues 4 u + g, u < U, g = l / 16, of integer
 // l % 16.  That is at once the second-operand and the accumulator layout of
@@ -62,13 +66,15 @@ __device__ __forceinline__ int rns_red(int64_t t, int m, int minv)
 constexpr int kDigitBias = 0x00808080;
 __device__ __forceinline__ int rns_digits(int biased) { return biased ^ kDigitBias; }
 
-// acc0 + 2^8 acc1 + 2^16 acc2 + 2^24 acc3 of a residue's four planes.
+// A residue's four planes acc0 + 2^8 acc1 + 2^16 acc2 + 2^24 acc3 as lo +
+// 2^16 hi, and as one value.
+__device__ __forceinline__ int rns_lo(v4i acc) { return acc[0] + (acc[1] << 8); }
+__device__ __forceinline__ int rns_hi(v4i acc) { return acc[2] + (acc[3] << 8); }
 __device__ __forceinline__ int64_t rns_planes(v4i acc)
 {
-    const int lo = acc[0] + (acc[1] << 8), hi = acc[2] + (acc[3] << 8);
     int k = 65536;
     asm("" : "+s"(k));                          // one multiply-add, not a 64-bit shift and add
-    return (int64_t)hi * k + lo;
+    return (int64_t)rns_hi(acc) * k + rns_lo(acc);
 }
 
 // Work split of a tile of 16 integers over W waves: wave v owns the units

@@ -95,11 +95,29 @@ class Config:
         assert 128 << bits <= 1 << (LIMB_BITS * limbs) and 3 * k // 4 + 1 <= 64
         self.w = [pow(self.B // p, -1, p) for p in b]
         self.ksteps = -(-units // 4)
+        self._check_accumulators()
+
+    def _check_accumulators(self) -> None:
+        """The plane accumulators of A -> B, combined in pairs (lo, hi) and
+        multiplied by words of at most 0.5 and 0.63 times 2^31, leave room for
+        the product they are added to (see rns_arith.hpp): with residues of at
+        most 0.9 * 2^31, |s kappa + lo v + hi v16| / 2^32 + m / 2 is below
+        that again."""
+        most = 0
+        for j in range(self.k):
+            planes = [0] * 4
+            for i in range(self.k):
+                for p in range(4):
+                    for r, d in enumerate(digits(centered(self.ext_ab(i, j) << (8 * p), self.b[j]))):
+                        planes[r] += 128 * abs(d)
+            most = max(most, planes[0] + 256 * planes[1] + 1.26 * (planes[2] + 256 * planes[3]))
+        s = 0.9 * 0.9 / 2 + 0.5                 # |s| / 2^31 for s = x y / 2^32
+        assert (s / 4 + most / 2 ** 33) + 0.5 < 0.9, (self.units, most)
 
     def ext_ab(self, i: int, j: int) -> int:
-        """A -> B: q = sum xi_i (A / a_i), scaled by A^-1 w_j 2^64."""
+        """A -> B: q = sum xi_i (A / a_i), scaled by A^-1 w_j 2^32."""
         m = self.b[j]
-        return (self.A // self.a[i]) * pow(self.A, -1, m) * self.w[j] * R * R % m
+        return (self.A // self.a[i]) * pow(self.A, -1, m) * self.w[j] * R % m
 
     def ext_ba(self, j: int, i: int) -> int:
         """B -> A: r = sum xi_j (B / b_j) - alpha B, scaled by 2^32."""
@@ -140,7 +158,7 @@ class Config:
     def residue_tables(self) -> Dict[str, List[int]]:
         """Per-residue constants, [group][unit] each."""
         t: Dict[str, List[int]] = {n: [] for n in ("MA", "NA", "MB", "NB", "KAPPA", "CINV", "R2A", "WR",
-                                                   "WONE")}
+                                                   "WONE", "V16")}
         for g in range(4):
             for u in range(self.units):
                 i = 4 * u + g
@@ -154,6 +172,7 @@ class Config:
                 t["R2A"].append(centered(R * R, a))
                 t["WR"].append(centered(w * R, b))
                 t["WONE"].append(centered(w, b))
+                t["V16"].append(centered(R << 16, b))
         return t
 
     def conversion(self, base: List[int]) -> List[int]:

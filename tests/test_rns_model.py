@@ -71,6 +71,7 @@ class Model:
         return x
 
     def extend(self, to_b, digits, alpha=None):
+        """(lo, hi) of every extended residue lo + 2^16 hi."""
         x = self.operand(digits, alpha)
         out = [0] * self.c.k
         for u in range(self.c.units):
@@ -78,13 +79,14 @@ class Model:
                 acc = [sum(a * b for a, b in zip(self.words[to_b][u][4 * g + r], x)) for r in range(4)]
                 lo, hi = acc[0] + (acc[1] << 8), acc[2] + (acc[3] << 8)
                 assert all(abs(v) < 1 << 31 for v in acc + [lo, hi])
-                out[4 * u + g] = (hi << 16) + lo
+                out[4 * u + g] = lo, hi
         return out
 
     def setup(self, n):
         c = self.c
         self.ci = [red(T.centered(pow(n, -1, a) * R, a) * self.t["CINV"][i], a) for i, a in enumerate(c.a)]
         self.v = [T.centered(n, b) for b in c.b]
+        self.v16 = [red(v * self.t["V16"][j], b) for j, (v, b) in enumerate(zip(self.v, c.b))]
 
     def enter(self, x):
         c = self.c
@@ -102,13 +104,14 @@ class Model:
         xb = []
         for j, b in enumerate(c.b):
             s = red(x[1][j] * y[1][j], b)
-            xb.append(red(s * self.t["KAPPA"][j] + red(q[j], b) * self.v[j], b))
-            assert -(1 << 31) <= xb[-1] + bias < 1 << 31
+            lo, hi = q[j]
+            xb.append(red(s * self.t["KAPPA"][j] + lo * self.v[j] + hi * self.v16[j], b))
+            assert abs(xb[-1]) < 0.9 * 2 ** 31 and xb[-1] + bias < 1 << 31
         dig = [T.digits(v) for v in xb]
         tops = self.operand(dig)
         self.alpha = (sum(a * b for a, b in zip(self.words[False][c.units][0], tops)) + 64) >> 7
         assert self.alpha == (sum(d[3] for d in dig) + 64) >> 7
-        xa = [red(v, c.a[i]) for i, v in enumerate(self.extend(False, dig, self.alpha))]
+        xa = [red((hi << 16) + lo, c.a[i]) for i, (lo, hi) in enumerate(self.extend(False, dig, self.alpha))]
         return xa, xb
 
     def value(self, x):
