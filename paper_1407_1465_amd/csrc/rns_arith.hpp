@@ -78,8 +78,8 @@ __device__ __forceinline__ int64_t rns_planes(v4i acc)
 }
 
 // Work split of a tile of 16 integers over W waves: wave v owns the units
-// v * UW .. v * UW + UW - 1 of each base (those from U on are padding) and
-// the extensions' row tiles of its units.
+// v, v + W, ... below U of each base, at most UW, and the extensions' row
+// tiles of its units.
 template <int U_, int W_>
 struct Rns {
     static constexpr int U = U_, W = W_;

@@ -12,8 +12,9 @@ namespace rsagpu {
 
 // ---- the exponentiation -------------------------------------------------------
 
-template <int U, int W>
-constexpr size_t rns_slot_words() { return 2 * (size_t)Rns<U, W>::UW * 64 * W; }
+// A table entry: 64 words per unit and base, those in A first.
+template <int U>
+constexpr size_t rns_slot_words() { return 2 * (size_t)U * 64; }
 // LDS words outside the table: with W > 1 the three operand exchange buffers,
 // and the flags of elements not to store.
 template <int U, int W>
@@ -24,7 +25,7 @@ template <int U, int W>
 constexpr size_t rns_lds_words(int w)
 {
     const size_t slots = (size_t)1 << (w - 1);
-    const size_t tab = slots * rns_slot_words<U, W>();
+    const size_t tab = slots * rns_slot_words<U>();
     const size_t need = 16 * (4 * U + 2) + 2 * 32 * (size_t)RnsTables<U>::LIMBS;
     return rns_fixed_words<U, W>() + (tab > need ? tab : need);
 }
@@ -44,14 +45,25 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
     using C = Rns<U, W>;
     using T = RnsTables<U>;
     constexpr int UW = C::UW, KS = C::KS, S = T::LIMBS, K = C::K, CH = rns_chunk<S>();
-    constexpr int SLOT = 2 * UW * 64;                    // words of one wave's part of a table entry
     uint32_t *lds = reinterpret_cast<uint32_t *>(rsagpu_lds);
-    const int wave = W == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int u0 = wave * UW;
+    int wave = W == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // Two workgroups share a CU at W = 4, and wave 0 has a unit more than the
+    // others where U = 13: turned by two in every other one, so that the long
+    // waves are not on one SIMD (4096 3072-bit decryptions 2075 -> 2037 us).
+    if constexpr (W == 4) wave = (wave + 2 * (int)((blockIdx.x ^ blockIdx.y) & 1)) & 3;
+    // units wave, wave + W, ...: the last is past U in the later waves where W
+    // does not divide U, and those pass over it (every wave worked on UW units
+    // at first, padding too: with 9 waves for 17 units the SIMD with a third
+    // wave had 6 units to do, now 5.  1092 4096-bit decryptions 2496 -> 2300
+    // us, 4096 of 3072 bits, 13 units on 4 waves, 2319 -> 2075).
+    constexpr bool kPadded = UW * W != U;
+    const bool full = !kPadded || wave + W * (UW - 1) < U;
+    auto unit_of = [&](int i) { return wave + W * i; };
     v4i *exch = reinterpret_cast<v4i *>(lds);            // [3][KS][64]
     uint32_t *nostore = lds + rns_fixed_words<U, W>() - 32;
     uint32_t *area = lds + rns_fixed_words<U, W>();
-    constexpr int STRIDE = SLOT * W;                     // words between table entries
+    constexpr int STRIDE = (int)rns_slot_words<U>();     // words between table entries
+    constexpr int UNIT = W * 64, BASE_B = U * 64;        // and within one, between a wave's units, and to base B
 
     if (src.idle()) return;
     unsigned long long tile = blockIdx.x;
@@ -61,7 +73,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
     // hoisted out of the loop over tiles, where it would not fit the registers
     if constexpr (Source::kLoop) asm volatile("" : "+v"(lane));
     const int g = lane >> 4;
-    int *tab = reinterpret_cast<int *>(area) + wave * SLOT + lane;
+    int *tab = reinterpret_cast<int *>(area) + wave * 64 + lane;
     const RnsJob job = src.job(tile, lane & 15);
     tile += gridDim.x;
     if (__ballot(job.live) == 0) continue;               // the same for every wave of the tile
@@ -79,7 +91,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
     int at[UW];
 #pragma unroll
     for (int i = 0; i < UW; ++i) {
-        const int u = u0 + i < U ? u0 + i : U - 1;       // padding repeats the last unit
+        const int u = unit_of(i) < U ? unit_of(i) : U - 1;       // padding repeats the last unit
         at[i] = g * U + u;
         ma[i] = (int)T::ma()[at[i]];
         na[i] = (int)T::na()[at[i]];
@@ -191,7 +203,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
     for (int i = 0; i < UW; ++i)
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            const int u = u0 + i < U ? u0 + i : U - 1;
+            const int u = unit_of(i) < U ? unit_of(i) : U - 1;
             eab[i][s] = C::matrix_word(T::eab(), u, s, lane);
             eba[i][s] = C::matrix_word(T::eba(), u, s, lane);
             asm volatile("" : "+a"(eab[i][s]), "+a"(eba[i][s]));
@@ -221,8 +233,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
             int sum = 0;
 #pragma unroll
             for (int i = 0; i < UW; ++i)
-                if (UW * W == U || u0 + i < U) {
-                    b[((u0 + i) / 4 * 64 + lane) * 4 + (u0 + i) % 4] = dig[i];
+                if (i < UW - 1 || full) {
+                    b[(unit_of(i) / 4 * 64 + lane) * 4 + unit_of(i) % 4] = dig[i];
                     sum += dig[i] >> 24;
                 }
             constexpr int at_alpha = U % 4;
@@ -238,6 +250,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
             }
         }
     };
+    auto each_unit = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < UW - (kPadded ? 1 : 0); ++i) f(i);
+        if constexpr (kPadded) {
+            if (full) f(UW - 1);
+        }
+    };
     // x = x * y * A^-1 mod n, y = x (SQR) or the table entry at yt.
     auto product = [&](auto SQR, const int *yt) {
         constexpr bool kSqr = decltype(SQR)::value;
@@ -250,24 +269,22 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
         int64_t bias = (int64_t)kDigitBias << 32;
         asm volatile("" : "+s"(bias));
         int dig[UW];
-#pragma unroll
-        for (int i = 0; i < UW; ++i) {
+        each_unit([&](int i) {
             int y = xa[i];
-            if constexpr (!kSqr) y = yt[i * 64];
+            if constexpr (!kSqr) y = yt[i * UNIT];
             const int s = rns_red((int64_t)xa[i] * y, ma[i], na[i]);
             dig[i] = rns_digits(rns_red((int64_t)s * c[i] + bias, ma[i], na[i]));
-        }
+        });
         v4i op[KS];
         exchange(op, dig, false);
-#pragma unroll
-        for (int i = 0; i < UW; ++i) {
+        each_unit([&](int i) {
             const v4i q = C::tile(eab[i], op);
             int y = xb[i];
-            if constexpr (!kSqr) y = yt[(UW + i) * 64];
+            if constexpr (!kSqr) y = yt[BASE_B + i * UNIT];
             const int s = rns_red((int64_t)xb[i] * y, mb[i], nb[i]);
             xb[i] = rns_red((int64_t)s * kap[i] + (int64_t)rns_lo(q) * v[i] + (int64_t)rns_hi(q) * v16[i], mb[i], nb[i]);
             dig[i] = rns_digits(xb[i] + kDigitBias);
-        }
+        });
         exchange(op, dig, true);
         // alpha, in lanes 0 .. 15 (zero elsewhere): unit U of the operand
         if constexpr (W == 1) alpha = (C::tile(esum, op)[0] + 64) >> 7;
@@ -275,23 +292,24 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
         op[KS - 1][U % 4] = alpha;
         v4i accs[UW];
 #pragma unroll
-        for (int i = 0; i < UW; ++i) accs[i] = C::tile(eba[i], op);
+        for (int i = 0; i < UW - (kPadded ? 1 : 0); ++i) accs[i] = C::tile(eba[i], op);
 #pragma unroll
-        for (int i = 0; i < UW; ++i) xa[i] = rns_red(rns_planes(accs[i]), ma[i], na[i]);
+        for (int i = 0; i < UW - (kPadded ? 1 : 0); ++i) xa[i] = rns_red(rns_planes(accs[i]), ma[i], na[i]);
+        if constexpr (kPadded) {
+            if (full) xa[UW - 1] = rns_red(rns_planes(C::tile(eba[UW - 1], op)), ma[UW - 1], na[UW - 1]);
+        }
     };
     auto put = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < UW; ++i) {
-            tab[slot * STRIDE + i * 64] = xa[i];
-            tab[slot * STRIDE + (UW + i) * 64] = xb[i];
-        }
+        each_unit([&](int i) {
+            tab[slot * STRIDE + i * UNIT] = xa[i];
+            tab[slot * STRIDE + BASE_B + i * UNIT] = xb[i];
+        });
     };
     auto get = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < UW; ++i) {
-            xa[i] = tab[slot * STRIDE + i * 64];
-            xb[i] = tab[slot * STRIDE + (UW + i) * 64];
-        }
+        each_unit([&](int i) {
+            xa[i] = tab[slot * STRIDE + i * UNIT];
+            xb[i] = tab[slot * STRIDE + BASE_B + i * UNIT];
+        });
     };
 
     constexpr std::true_type SQUARE{};
@@ -373,11 +391,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
         }
     }
     // times one: leave the Montgomery domain
-#pragma unroll
-    for (int i = 0; i < UW; ++i) {
-        tab[i * 64] = 1;
-        tab[(UW + i) * 64] = (int)T::wone()[at[i]];
-    }
+    each_unit([&](int i) {
+        tab[i * UNIT] = 1;
+        tab[BASE_B + i * UNIT] = (int)T::wone()[at[i]];
+    });
     product(TIMES, tab);
 
     // ---- the way out: x = sum_j xb_j (B / b_j) - alpha B in 29-bit limbs,
@@ -387,7 +404,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) v
     else lds_sync();
 #pragma unroll
     for (int i = 0; i < UW; ++i)
-        if (UW * W == U || u0 + i < U) res[(lane & 15) * (K + 1) + 4 * (u0 + i) + g] = (uint32_t)(xb[i] + mb[i]);
+        if (i < UW - 1 || full) res[(lane & 15) * (K + 1) + 4 * unit_of(i) + g] = (uint32_t)(xb[i] + mb[i]);
     if (wave == 0 && lane < 16) res[lane * (K + 1) + K] = (uint32_t)(alpha + K);
     if constexpr (W > 1) __syncthreads();
     else lds_sync();
