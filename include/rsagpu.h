@@ -273,8 +273,7 @@ int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, const uint32_t
 /*
  * Streams an rsa_ops_batch call forks its widest CRT buckets onto (0 to 3,
  * default 3), beside the caller's stream, which runs every other bucket and
- * then waits for the forks; calls of at least 16384 operations use at most
- * two.  Each caller stream has a fork set of its own
+ * then waits for the forks.  Each caller stream has a fork set of its own
  * (up to 8 caller streams per keyset; further callers, and a caller first
  * seen while it is being captured into a graph, run unforked), so calls on
  * different caller streams overlap on the device.  A process has 4 hardware

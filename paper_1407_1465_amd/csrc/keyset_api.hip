@@ -173,6 +173,7 @@ struct rsa_keyset {
         int made;                       // streams (and their events) created so far
         hipStream_t streams[kStreams];
         hipEvent_t fork;
+        hipEvent_t entered[kStreams];   // a bucket's tiles may be placed (bulk batches)
         hipEvent_t done[kStreams];
     };
     ForkSet forksets[kForkSets];
@@ -272,6 +273,7 @@ extern "C" int rsa_keyset_destroy(rsa_keyset *ks)
         rsa_keyset::ForkSet &f = ks->forksets[i];
         for (int t = 0; t < f.made; ++t) {
             (void)hipStreamDestroy(f.streams[t]);
+            (void)hipEventDestroy(f.entered[t]);
             (void)hipEventDestroy(f.done[t]);
         }
         (void)hipEventDestroy(f.fork);
@@ -401,16 +403,20 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     // waves also raise their issue priority: every call ends with its
     // operations, whose chains are the longest, so on a SIMD shared with other
     // buckets' waves they issue first.
-    // In a bulk batch only the two widest fork, and the other CRT buckets follow
-    // the encryptions: a wide bucket's workgroups (nine or four waves) find no
-    // CU with room once one-wave tiles of a narrow bucket fill the SIMDs, so
-    // they get the encryptions' time as a start (mixed 32768-operation batch
-    // with three forks and the encryptions last 7.65 ms, now 7.2 ms).
+    // In a bulk batch, whose buckets fill the chip, the forked buckets and then
+    // the caller's stream start one after the other, widest first, each once
+    // the tiles of the one before may be placed: a wide bucket's workgroups
+    // (nine or four waves, most of a CU's LDS) find no CU with room while
+    // one-wave tiles of a narrow bucket take up every SIMD that falls free
+    // (mixed 32768-operation batch, the 4096-bit bucket's tiles done last: 5.95
+    // ms with the forks started together, 5.1 in turn; a smaller batch does
+    // not fill the chip and would only wait).  The CRT buckets beyond the
+    // streams follow the encryptions there (before them: 5.3 ms).
     const bool bulk = nops >= kBulkOps;
     int order[kMaxBuckets], nb = 0, crt[kMaxBuckets], ncrt = 0;
     for (int cls = num_classes() - 1; cls >= 0; --cls)
         if (mask & (1u << cls)) crt[ncrt++] = cls * 2 + 1;
-    const int first = bulk && ncrt > 2 ? 2 : ncrt;
+    const int first = bulk && ncrt > rsa_keyset::kStreams ? rsa_keyset::kStreams : ncrt;
     for (int i = 0; i < first; ++i) order[nb++] = crt[i];
     for (int i = 0; i < ncrt; ++i) order[nb++] = crt[i] - 1;
     for (int i = first; i < ncrt; ++i) order[nb++] = crt[i];
@@ -457,7 +463,7 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     // overlap the large ones.
     std::lock_guard<std::mutex> launch_lock(ks->launch_mu);
     rsa_keyset::ForkSet *fs = nullptr;
-    int nfork = bulk && ks->forks > 2 ? 2 : ks->forks;
+    int nfork = ks->forks;
     if (nfork > 0) {
         for (int i = 0; i < ks->nforksets; ++i)
             if (ks->forksets[i].caller == stream) fs = &ks->forksets[i];
@@ -482,24 +488,32 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
                     (void)hipStreamDestroy(fs->streams[fs->made]);
                     return RSA_EHIP;
                 }
+                if (hipEventCreateWithFlags(&fs->entered[fs->made], hipEventDisableTiming) != hipSuccess) {
+                    (void)hipEventDestroy(fs->done[fs->made]);
+                    (void)hipStreamDestroy(fs->streams[fs->made]);
+                    return RSA_EHIP;
+                }
             }
         }
         nfork = fs ? (nfork < fs->made ? nfork : fs->made) : 0;    // no fork set: every bucket on `stream`
     }
     if (nfork > 0 && (e = hipEventRecord(fs->fork, stream)) != hipSuccess) return status_of(e);
     int forked = 0;
+    hipEvent_t turn = nullptr;
     for (int t = 0; t < nb; ++t) {
         const int b = order[t], kind = b % 2;
         const Resolved &r = plan[t];
         const bool fork = kind == 1 && t < nfork;
         hipStream_t s = fork ? fs->streams[t] : stream;
         if (fork && (e = hipStreamWaitEvent(s, fs->fork, 0)) != hipSuccess) return status_of(e);
+        if (turn && (fork || t == forked) && (e = hipStreamWaitEvent(s, turn, 0)) != hipSuccess) return status_of(e);
         if (rns[t]) {
             // the bucket with its runs rounded up to whole tiles
             const size_t padded = nops + (round_runs ? (size_t)kKeySlots * 15 : 0);
             const RnsOpsArgs a{ks->keys, od, lists + (size_t)b * cap, counts + b, in_pool, out_pool,
-                               padded < cap ? padded : cap, cus, bulk};
+                               padded < cap ? padded : cap, cus, bulk, fork && bulk ? fs->entered[t] : nullptr};
             if ((e = rns[t](a, s)) != hipSuccess) return status_of(e);
+            if (a.entered) turn = a.entered;
             if (fork) {
                 if ((e = hipEventRecord(fs->done[t], s)) != hipSuccess) return status_of(e);
                 ++forked;

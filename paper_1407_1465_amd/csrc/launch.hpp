@@ -140,6 +140,7 @@ struct RnsOpsArgs {
     size_t most;                      // its size is at most this
     int cus;
     bool bulk;                        // of a bulk batch (kBulkOps)
+    hipEvent_t entered;               // if not null, recorded once the way in is done
 };
 typedef hipError_t (*rns_ops_launcher)(const RnsOpsArgs &, hipStream_t);
 typedef hipError_t (*rns_crt_launcher)(const RnsCrtArgs &, hipStream_t);

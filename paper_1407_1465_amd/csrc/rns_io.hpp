@@ -415,7 +415,8 @@ hipError_t launch_rns_ops(const RnsOpsArgs &a, hipStream_t stream)
                        a.ops, a.list, a.size, a.in_pool, a.out_pool);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const RnsOpsSource<false> src{a.keys, a.ops, a.list, a.size, a.out_pool, 0, 0};
+    if (a.entered && (e = hipEventRecord(a.entered, stream)) != hipSuccess) return e;
+    const RnsOpsSource src{a.keys, a.ops, a.list, a.size, a.out_pool, 0, ~0u, 0};
     e = rns_pow_bucket<U>(src, (a.most + 15) / 16, a.bulk, a.cus, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_rns_leave_ops<S, G>), blocks(ng * kIoWaves), dim3(64 * kIoWaves), lds, stream, a.keys, a.ops,

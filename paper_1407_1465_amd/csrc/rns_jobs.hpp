@@ -109,23 +109,23 @@ struct RnsExpSource {
 // blockIdx.y is the half.  The bucket is this launch's where its tiles number
 // above `above` and at most `upto` (launches of several shapes follow each
 // other, and the bucket's size picks one).
-template <bool LOOP>
 struct RnsOpsSource {
     const KeyDev *keys;
     const OpDesc *ops;
     const unsigned *list, *size;
     uint32_t *out_pool;
     unsigned above, upto;
-    static constexpr bool kLoop = LOOP;
+    unsigned skip;                      // tiles before the launch's first
+    static constexpr bool kLoop = false;
     __device__ __forceinline__ unsigned long long tiles() const
     {
         const unsigned t = (*size + 15u) / 16u;
         return t > above && t <= upto ? t : 0u;
     }
-    __device__ __forceinline__ bool idle() const { return blockIdx.x >= tiles(); }
+    __device__ __forceinline__ bool idle() const { return blockIdx.x + skip >= tiles(); }
     __device__ __forceinline__ RnsJob job(unsigned long long tile, int i) const
     {
-        const unsigned first = (unsigned)tile * 16u, idx = first + (unsigned)i;
+        const unsigned first = ((unsigned)tile + skip) * 16u, idx = first + (unsigned)i;
         const unsigned at = idx < *size ? list[idx] : kOrderHole;
         RnsJob j;
         j.live = at != kOrderHole;
@@ -149,6 +149,6 @@ template <int U>
 hipError_t rns_pow(const RnsExpSource<false> &src, size_t tiles, unsigned halves, int cus, hipStream_t stream);
 // ... over a bucket of at most `tiles` tiles.
 template <int U>
-hipError_t rns_pow_bucket(const RnsOpsSource<false> &src, size_t tiles, bool bulk, int cus, hipStream_t stream);
+hipError_t rns_pow_bucket(const RnsOpsSource &src, size_t tiles, bool bulk, int cus, hipStream_t stream);
 
 }  // namespace rsagpu

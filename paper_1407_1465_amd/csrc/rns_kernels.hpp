@@ -512,53 +512,44 @@ hipError_t launch_rns_tiles(const Source &src, size_t tiles, unsigned halves, in
         if constexpr (Source::kExp) return launch_rns_pow<U, 1, 1>(src.looping(), resident(4), 4, stream);
         return launch_rns_pow<U, 1, 1>(src, grid, 4, stream);
     } else if constexpr (U == 13) {
-        if (all <= cu) return launch_rns_pow<U, 13, 4>(src, grid, 5, stream);
-        if constexpr (Source::kExp) return launch_rns_pow<U, 4, 2>(src.looping(), resident(2), 4, stream);
-        return launch_rns_pow<U, 4, 2>(src, grid, 4, stream);
+        if (Source::kExp || all <= cu) return launch_rns_pow<U, 13, 4>(src, grid, 5, stream);
+        if constexpr (!Source::kExp) return launch_rns_pow<U, 4, 2>(src, grid, 4, stream);
     } else {
         static_assert(U == 17, "a configuration of rns_tables.py");
         return launch_rns_pow<U, 9, 2>(src, grid, 5, stream);
     }
 }
 
-// The halves of an ops batch's CRT bucket, whose size only the device knows.  A
-// bulk batch takes the shape for many tiles, whatever a bucket holds.  For a
-// smaller batch both shapes are launched, and the bucket's size decides which
-// one's workgroups end at once (beside other buckets' waves even those wait
-// for a CU with room: in a bulk batch the empty launches of nine-wave
-// workgroups held the 2048-bit bucket back by 3 ms).
+// The halves of an ops batch's CRT bucket, whose size only the device knows:
+// a workgroup for each tile it may have, of which those past the end leave at
+// once (the resident workgroups taking several tiles each, in strides set
+// before the others' speed is known, made three rounds out of two beside other
+// buckets: mixed 32768-operation batch 6.2 ms, now 5.95).  A bulk batch takes
+// the shape for many tiles, whatever a bucket holds.  For a smaller batch both
+// shapes are launched, and the bucket's size decides which one's workgroups
+// leave (beside other buckets' waves even those wait for a CU with room: in a
+// bulk batch the empty launches of nine-wave workgroups held the 2048-bit
+// bucket back by 3 ms).
+constexpr size_t kBucketTiles = (size_t)1 << 20;     // a launch (2^32 threads a dimension at most)
 template <int U>
-hipError_t launch_rns_bucket(const RnsOpsSource<false> &src, size_t tiles, bool bulk, int cus, hipStream_t stream)
+hipError_t launch_rns_bucket(RnsOpsSource src, size_t tiles, bool bulk, int cus, hipStream_t stream)
 {
-    const unsigned cu = (unsigned)(cus > 0 ? cus : 1), few = bulk ? 0 : cu / 2;
-    RnsOpsSource<false> lo = src;
-    lo.above = 0;
-    lo.upto = few;
-    const RnsOpsSource<true> hi{src.keys, src.ops, src.list, src.size, src.out_pool, few, ~0u};
-    const dim3 glo((unsigned)(tiles < few ? tiles : few), 2);
-    const auto ghi = [&](unsigned per_cu) {
-        const unsigned most = per_cu * cu / 2;
-        return dim3(tiles < most ? (unsigned)tiles : most, 2);
-    };
+    const size_t few = bulk ? 0 : (size_t)(cus > 1 ? cus : 2) / 2;
     hipError_t e = hipSuccess;
-    if constexpr (U == 5) {
-        RnsOpsSource<true> all = hi;
-        all.above = 0;
-        return launch_rns_pow<U, 1, 1>(all, ghi(4), 4, stream);
-    } else if constexpr (U == 7) {
-        if (!bulk) e = launch_rns_pow<U, 7, 4>(lo, glo, 4, stream);
-        if (e == hipSuccess && tiles > few) e = launch_rns_pow<U, 1, 1>(hi, ghi(4), 4, stream);
-    } else if constexpr (U == 9) {
-        if (!bulk) e = launch_rns_pow<U, 9, 4>(lo, glo, 5, stream);
-        if (e == hipSuccess && tiles > few) e = launch_rns_pow<U, 1, 1>(hi, ghi(4), 4, stream);
-    } else if constexpr (U == 13) {
-        if (!bulk) e = launch_rns_pow<U, 13, 4>(lo, glo, 5, stream);
-        if (e == hipSuccess && tiles > few) e = launch_rns_pow<U, 4, 2>(hi, ghi(2), 4, stream);
-    } else {
-        RnsOpsSource<false> all = src;
-        all.above = 0;
-        all.upto = ~0u;
-        return launch_rns_pow<U, 9, 2>(all, dim3((unsigned)tiles, 2), 5, stream);
+    if constexpr (U == 7 || U == 9 || U == 13) {
+        constexpr int w = U == 7 ? 4 : 5;
+        src.upto = (unsigned)few;
+        if (few) e = launch_rns_pow<U, U, 4>(src, dim3((unsigned)(tiles < few ? tiles : few), 2), w, stream);
+        if (e != hipSuccess || tiles <= few) return e;
+        src.above = (unsigned)few;
+        src.upto = ~0u;
+    }
+    for (size_t at = 0; at < tiles && e == hipSuccess; at += kBucketTiles) {
+        const dim3 grid((unsigned)(tiles - at < kBucketTiles ? tiles - at : kBucketTiles), 2);
+        src.skip = (unsigned)at;
+        if constexpr (U == 17) e = launch_rns_pow<U, 9, 2>(src, grid, 5, stream);
+        else if constexpr (U == 13) e = launch_rns_pow<U, 4, 2>(src, grid, 4, stream);
+        else e = launch_rns_pow<U, 1, 1>(src, grid, 4, stream);
     }
     return e;
 }
@@ -575,7 +566,7 @@ hipError_t launch_rns_bucket(const RnsOpsSource<false> &src, size_t tiles, bool 
         return launch_rns_tiles<U_>(src, tiles, halves, cus, stream);                                           \
     }                                                                                                           \
     template <>                                                                                                 \
-    hipError_t rns_pow_bucket<U_>(const RnsOpsSource<false> &src, size_t tiles, bool bulk, int cus,             \
+    hipError_t rns_pow_bucket<U_>(const RnsOpsSource &src, size_t tiles, bool bulk, int cus,             \
                                   hipStream_t stream)                                                           \
     {                                                                                                           \
         return launch_rns_bucket<U_>(src, tiles, bulk, cus, stream);                                            \
