@@ -7,6 +7,11 @@
 // The intermediate integers live in the caller's output words, so no call
 // needs scratch memory.
 //
+// The positional kernels are bound by their own chains (a wave's Montgomery
+// set-up, some 30 products), not by memory: of 2159 us for 16384 2048-bit
+// decryptions the way in takes 72 and the way out 36, of 711 us for few
+// messages 38 and 27.
+//
 // A modulus that shares a factor with base A has no inverse there (a random
 // one, odds 2^-25); k_rns_enter_* finds such elements, exponentiates them
 // positionally and leaves the result; k_rns_pow finds them again (a zero

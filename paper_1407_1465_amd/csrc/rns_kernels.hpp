@@ -38,7 +38,18 @@ constexpr size_t rns_lds_words(int w)
 // 7% more products, in lockstep, where a schedule per integer multiplied each
 // by itself or an entry as its turn came and kept the scans of 16 exponents
 // in every step (200 2048-bit exponentiations with their own exponents: 4880
-// us; now 2741).
+// us; now 2721).
+//
+// What bounds it: issue.  A product of a tile of 32-word integers (U = 9) on
+// one wave is 57 matrix instructions (16 cycles each) and about 245 others in
+// 1957 cycles: with one wave on a SIMD the two do not overlap (only a run of
+// eight or more vector instructions hides a matrix instruction, and there are
+// 4.3 for each; moving the next product's first half under the second
+// extension, 1 matrix to 3 .. 5 vector instructions, 2333 -> 2344 .. 2601 us
+// for 16384 2048-bit decryptions).  Both matrices, 228 registers of each
+// lane, leave no room for a second wave on the SIMD; two waves a tile have it
+// and pay two exchanges a product (3366 us).  16384 2048-bit decryptions,
+// 2048 tiles: 3550 us positionally, now 2159; 1092 of 4096 bits 6277 -> 2304.
 template <int U, int W, int OCC, typename Source>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(OCC))) void k_rns_pow(Source src, int w)
 {
@@ -483,13 +494,15 @@ hipError_t launch_rns_pow(const Source &src, dim3 grid, int w, hipStream_t strea
 // (one or two residues per lane and base each) where every tile has a CU of
 // its own, and one wave, or the fewest whose matrices fit the registers,
 // where the tiles fill the chip.  CRT decryptions, us: 2048-bit keys, 5
-// messages 1153 with one wave, 828 with 3, 749 with 9; 4096 messages (512
-// tiles) 1278, 1231 and (9 waves) two rounds; 16384 messages 2427 with one
-// and 3402 with 3 waves.  3072-bit keys, 777 messages (114 tiles) 1467 with
-// 13 waves, 1580 with 7, 1779 with 5; 4096 messages 2280 with 4 and 3078
-// with 7.  4096-bit keys, 1092 messages 2582 with 9 waves, 2772 with 6, 3049
-// with 4; 4368 messages 7732 with 9, 8252 with 6 and 8892 with 4.  The window
-// is the widest whose table leaves LDS for the workgroups a CU is to hold.
+// messages 1153 with one wave, 828 with 3, 711 with 9; 4096 messages (512
+// tiles) 1278 with one, 1103 with 3, 1099 with 4 and (9 waves) two rounds;
+// 16384 messages 2159 with one and 3402 with 3.  3072-bit keys, 777 messages
+// (114 tiles) 1454 with 13 waves, 1580 with 7, 1779 with 5; 4096 messages 2037
+// with 4 waves (two tiles a CU; 3416 with one), 2492 with 2, 3357 with 5, 3889
+// with 3; 16384 messages 8123 with 4 and 9678 with 2.  4096-bit keys, 1092
+// messages 2301 with 9 waves, 2330 with 8, 2353 with 12; 4368 messages 6463,
+// 6517 and 6643 (6 and 4 waves were 6 and 18% above 9).  The window is the
+// widest whose table leaves LDS for the workgroups a CU is to hold.
 template <int U, typename Source>
 hipError_t launch_rns_tiles(const Source &src, size_t tiles, unsigned halves, int cus, hipStream_t stream)
 {
@@ -512,8 +525,9 @@ hipError_t launch_rns_tiles(const Source &src, size_t tiles, unsigned halves, in
         if constexpr (Source::kExp) return launch_rns_pow<U, 1, 1>(src.looping(), resident(4), 4, stream);
         return launch_rns_pow<U, 1, 1>(src, grid, 4, stream);
     } else if constexpr (U == 13) {
-        if (Source::kExp || all <= cu) return launch_rns_pow<U, 13, 4>(src, grid, 5, stream);
-        if constexpr (!Source::kExp) return launch_rns_pow<U, 4, 2>(src, grid, 4, stream);
+        if (all <= cu) return launch_rns_pow<U, 13, 4>(src, grid, 5, stream);
+        if constexpr (Source::kExp) return launch_rns_pow<U, 4, 2>(src.looping(), resident(2), 4, stream);
+        return launch_rns_pow<U, 4, 2>(src, grid, 4, stream);
     } else {
         static_assert(U == 17, "a configuration of rns_tables.py");
         return launch_rns_pow<U, 9, 2>(src, grid, 5, stream);

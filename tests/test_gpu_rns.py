@@ -75,6 +75,7 @@ def test_modexp_edges(limbs, shared):
 # one wave per residue, three waves, one wave (several tiles per workgroup)
 @pytest.mark.parametrize("limbs,count", [(16, 1000), (24, 16 * 256), (24, 16 * 256 + 1), (32, 16 * 256), (32, 16 * 257),
                                          (32, 16 * 512 + 3), (32, 16 * 1024 + 17), (48, 16 * 256), (48, 16 * 256 + 1),
+                                         (48, 16 * 512 + 3),
                                          (64, 300)])
 def test_modexp_launch_shapes(limbs, count):
     rng = random.Random(limbs + count)
