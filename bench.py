@@ -286,6 +286,15 @@ def measured_traffic(kernel):
     return t.get("traffic_bytes_per_launch")
 
 
+def pow_kernel(name, words, plan):
+    """The kernel that exponentiates modulo `words` words: `name` under `plan`,
+    or, at 13 to 64 words (the default plans), the RNS kernel, whose products
+    run on the matrix cores."""
+    if 12 < words <= 64:
+        return "k_rns_pow"
+    return "%s<%d,%d,%d>" % (name, plan.padded_limbs, plan.lanes_per_op, plan.radix_bits)
+
+
 def roofline(products, ms, kernel, per_unit=None, units=None, as_run=None, peak=None):
     """Roofline object of the dominant kernel: `products` algorithmic 32x32-bit
     products per launch (per_unit x units) over `ms` per launch; `as_run` the
@@ -300,6 +309,9 @@ def roofline(products, ms, kernel, per_unit=None, units=None, as_run=None, peak=
         r["as_run"] = {"products_per_launch": as_run, "frac": as_run / (ms / 1e3) / INT32_MUL_PEAK,
                        "count": "sliding window as run, squarings at the symmetric cost where the kernel "
                                 "squares with one product per limb pair"}
+        if kernel == "k_rns_pow":
+            r["as_run"]["count"] = ("the positional kernel's schedule under this plan, for comparison (the RNS "
+                                    "kernel's products are matrix instructions)")
     if peak is not None:
         r["peak_measured"] = {"value": peak["ops_per_s"] / 1e12, "unit": "T int32-mul/s", "op": peak["op"],
                               "frac_of_nominal": peak["ops_per_s"] / INT32_MUL_PEAK}
@@ -572,10 +584,8 @@ def main():
                                 "window_bits": plan.window_bits, "lanes_per_op": plan.lanes_per_op,
                                 "waves_per_workgroup": 4 if plan.lanes_per_op >= 8 else 2})
             per_unit = unit_crt_products(h)
-            line["roofline"] = roofline(per_unit * count, ms, "k_crt<%d,%d,%d>" % (plan.padded_limbs,
-                                                                                   plan.lanes_per_op,
-                                                                                   plan.radix_bits),
-                                        per_unit, count, as_run, measured_peak())
+            line["roofline"] = roofline(per_unit * count, ms, pow_kernel("k_crt", h, plan), per_unit, count, as_run,
+                                        measured_peak())
             if args.cpu_sample:
                 import oracle
                 cpu = cpu_baseline(oracle, wl.ctxt, d_h, n_h, out.cpu().numpy().view(np.uint32), "decryptions/s",
@@ -643,10 +653,8 @@ def main():
                     config={"workload": wl.name + "-decrypt", "messages": count, "radix_bits": plan.radix_bits,
                             "window_bits": plan.window_bits, "lanes_per_op": plan.lanes_per_op})
         per_unit = unit_exp_products(L)
-        line["roofline"] = roofline(per_unit * count, ms, "k_modexp<%d,%d,%d>" % (plan.padded_limbs,
-                                                                                  plan.lanes_per_op,
-                                                                                  plan.radix_bits),
-                                    per_unit, count, as_run, measured_peak())
+        line["roofline"] = roofline(per_unit * count, ms, pow_kernel("k_modexp", L, plan), per_unit, count, as_run,
+                                    measured_peak())
         if L <= 2:
             line["roofline"]["note"] = "launch-bound: one launch of ~80 dependent products"
         if args.cpu_sample:
