@@ -175,7 +175,13 @@ __global__ __launch_bounds__(64 * kIoWaves) RSAGPU_EXP_OCC(S / G) void k_rns_ent
     const bool live = msg < count;
     const size_t off = live ? (size_t)msg * (size_t)limbs : 0;
     uint32_t upper = 0;
-    for (int k = kRnsMinBits / 32 + r; k < limbs; k += G) upper |= live ? exp[off + k] : 0u;
+    // unrolled, so that no load waits for another: 1000 2048-bit encryptions
+    // 139 -> 131 us
+#pragma unroll
+    for (int i = 0; kRnsMinBits / 32 + i * G < S * 29 / 32; ++i) {
+        const int k = kRnsMinBits / 32 + r + i * G;
+        upper |= live && k < limbs ? exp[off + k] : 0u;
+    }
 
     uint32_t n[L], x[L];
     Ar::load(n, mod + off, limbs, 0, live);
