@@ -18,9 +18,9 @@
  *     asynchronous: the call returns before the results exist.  No entry
  *     point synchronises the device except rsa_device_errors.
  *   - Operands and the window table of each exponentiation live in
- *     registers and LDS.  Calls of several kernels pass intermediate integers
- *     through the output words, which hold them until the call's work on the
- *     stream is done.  No entry point allocates device memory per call:
+ *     registers and LDS.  Plain calls of several kernels pass intermediate
+ *     integers through their output words, which hold them until the call's
+ *     work on the stream is done; rsa_ops_batch through its workspace.  No entry point allocates device memory per call:
  *     rsa_modexp_batch needs no scratch, rsa_ops_batch takes a caller
  *     workspace, and rsa_decrypt_crt_batch keeps one key-ordering buffer per
  *     device and stream handle, made the first time that stream needs one
@@ -262,9 +262,13 @@ size_t rsa_ops_workspace_size(size_t max_ops);
  * out_pool[out_off ..] = in_pool[in_off ..]^(e or d) mod n of its key, each
  * range the key's limbs words; the input must be < n.  in_words / out_words
  * bound the pools: an operation whose kind, key id or ranges are invalid is
- * skipped and counted as a data error.  workspace: caller-owned device
- * memory of at least rsa_ops_workspace_size(nops) bytes; calls that overlap
- * in time must use different workspaces.  nops < 2^32 (RSA_EINVAL beyond).
+ * skipped and counted as a data error.  Operations may share an output range:
+ * each of its words is then that of one of their results (copies of one
+ * operation, whose input is elsewhere, all write the same).  workspace:
+ * caller-owned device memory of at least rsa_ops_workspace_size(nops) bytes
+ * (one of at least 33024 + 128 * nops bytes is taken too: its CRT buckets
+ * then run on the positional kernels); calls that overlap in time must use
+ * different workspaces.  nops < 2^32 (RSA_EINVAL beyond).
  * Asynchronous on `stream`.
  */
 int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, const uint32_t *in_pool, size_t in_words,

@@ -17,8 +17,10 @@ static_assert(sizeof(OpDesc) == sizeof(rsa_op), "rsa_op layout");
 static const int kMaxBuckets = 32;            // 2 kinds x width classes
 static const int kKeySlots = 256;             // key ids per bucket ordered apart (id mod 256)
 // workspace header: per bucket its size and claim counter, then per bucket
-// and key slot a count that becomes a list cursor
+// and key slot a count that becomes a list cursor; then the lists, and last,
+// per operation, what passes between the kernels of an RNS bucket
 static const size_t kWsHeader = (2 * kMaxBuckets + (size_t)kMaxBuckets * kKeySlots) * sizeof(unsigned);
+static const size_t kWsList = (size_t)kMaxBuckets * sizeof(unsigned), kWsMid = kMidWords * sizeof(uint32_t);
 
 // ---- bucketing kernels -------------------------------------------------------
 //
@@ -366,7 +368,7 @@ extern "C" int rsa_keyset_add(rsa_keyset *ks, int limbs, const uint32_t *n, cons
 
 extern "C" size_t rsa_ops_workspace_size(size_t max_ops)
 {
-    return kWsHeader + (size_t)kMaxBuckets * max_ops * sizeof(unsigned);
+    return kWsHeader + (kWsList + kWsMid) * max_ops;
 }
 
 extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, const uint32_t *in_pool,
@@ -377,16 +379,19 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     if (nops == 0) return RSA_OK;
     // operation indices and bucket counts are 32-bit on the device
     if (nops > 0xffffffffull) return RSA_EINVAL;
-    if (!ops || !in_pool || !out_pool || !workspace || ws_bytes < rsa_ops_workspace_size(nops)) return RSA_EINVAL;
+    if (!ops || !in_pool || !out_pool || !workspace || ws_bytes < kWsHeader + kWsList * nops) return RSA_EINVAL;
+    // a workspace that holds the lists alone: every bucket runs positionally
+    const size_t mid_bytes = ws_bytes >= rsa_ops_workspace_size(nops) ? kWsMid * nops : 0;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev != ks->device) return RSA_EINVAL;
     unsigned long long *errs = nullptr;
     int st = device_state(&errs);
     if (st != RSA_OK) return st;
-    const size_t cap = (ws_bytes - kWsHeader) / ((size_t)kMaxBuckets * sizeof(unsigned));
+    const size_t cap = (ws_bytes - kWsHeader - mid_bytes) / kWsList;
     unsigned *hdr = static_cast<unsigned *>(workspace);
     unsigned *counts = hdr, *counters = hdr + kMaxBuckets, *slots = hdr + 2 * kMaxBuckets;
     unsigned *lists = slots + (size_t)kMaxBuckets * kKeySlots;
+    uint32_t *mid = lists + (size_t)kMaxBuckets * cap;
     int nkeys;
     unsigned mask;
     {
@@ -437,7 +442,7 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
         // where the LDS holds them (see crt_pairs)
         const Instance *in = plan[t].inst;
         pairs[t] = kind == 1 && bulk && crt_lds_fits(in->S, in->G, in->B, plan[t].w, 2) ? 2 : 1;
-        rns[t] = kind == 1 ? rns_ops_of(width, pkind) : nullptr;
+        rns[t] = kind == 1 && mid_bytes ? rns_ops_of(width, pkind) : nullptr;
         if (kind == 1 && round_runs) units.u[b] = rns[t] ? 16u : (unsigned)(64 / plan[t].inst->G);
     }
     const unsigned op_blocks = (unsigned)((nops + 255) / 256);
@@ -510,7 +515,7 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
         if (rns[t]) {
             // the bucket with its runs rounded up to whole tiles
             const size_t padded = nops + (round_runs ? (size_t)kKeySlots * 15 : 0);
-            const RnsOpsArgs a{ks->keys, od, lists + (size_t)b * cap, counts + b, in_pool, out_pool,
+            const RnsOpsArgs a{ks->keys, od, lists + (size_t)b * cap, counts + b, in_pool, out_pool, mid,
                                padded < cap ? padded : cap, cus, bulk, fork && bulk ? fs->entered[t] : nullptr};
             if ((e = rns[t](a, s)) != hipSuccess) return status_of(e);
             if (a.entered) turn = a.entered;

@@ -131,12 +131,17 @@ struct RnsExpArgs {
     int limbs, cus, window;
     unsigned long long *errs;
 };
+// Words of an operation between the kernels of its bucket (both its halves, of
+// at most 64 words): not in its output, which another operation of the batch
+// may share (copies of one operation that fill a batch up, for instance).
+constexpr size_t kMidWords = 128;
 struct RnsOpsArgs {
     const KeyDev *keys;
     const OpDesc *ops;
     const unsigned *list, *size;      // the bucket (device)
     const uint32_t *in_pool;
     uint32_t *out_pool;
+    uint32_t *mid;                    // kMidWords words per operation, between the kernels
     size_t most;                      // its size is at most this
     int cus;
     bool bulk;                        // of a bulk batch (kBulkOps)

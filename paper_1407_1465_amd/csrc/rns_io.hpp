@@ -4,8 +4,9 @@
 // (positional, lane groups of radix_bn.hpp) turns each input x into x * A
 // mod n, the Montgomery form for base A, k_rns_pow (rns_kernels.hpp)
 // exponentiates it in RNS, and for CRT k_rns_leave_crt recombines the halves.
-// The intermediate integers live in the caller's output words, so no call
-// needs scratch memory.
+// The intermediate integers of a plain call live in the caller's output words,
+// so it needs no scratch memory; those of an ops batch, whose operations may
+// name the same output, in its workspace.
 //
 // The positional kernels are bound by their own chains (a wave's Montgomery
 // set-up, some 30 products), not by memory: of 2159 us for 16384 2048-bit
@@ -297,7 +298,8 @@ __global__ __launch_bounds__(64 * kIoWaves) void k_rns_enter_ops(const KeyDev *_
                                                                  const OpDesc *__restrict__ ops,
                                                                  const unsigned *__restrict__ list,
                                                                  const unsigned *__restrict__ size,
-                                                                 const uint32_t *in_pool, uint32_t *out_pool)
+                                                                 const uint32_t *__restrict__ in_pool,
+                                                                 uint32_t *__restrict__ mid)
 {
     using Ar = Arith<S, G, 29>;
     constexpr int L = S / G, NG = 64 / G;
@@ -310,7 +312,8 @@ __global__ __launch_bounds__(64 * kIoWaves) void k_rns_enter_ops(const KeyDev *_
         const unsigned idx = first + (wave >> 1) * NG + grp_index<G>();
         const unsigned at = idx < count ? list[idx] : kOrderHole;
         const bool live = at != kOrderHole;
-        const OpDesc &op = ops[live ? at : list[first]];         // the first entry of a run of tiles is no hole
+        const unsigned o = live ? at : list[first];              // the first entry of a run of tiles is no hole
+        const OpDesc &op = ops[o];
         const KeyDev &k = keys[op.key_id];
         const int hl = k.hwords;
         const ModConsts &mc = half ? k.cq[1] : k.cp[1];
@@ -337,8 +340,7 @@ __global__ __launch_bounds__(64 * kIoWaves) void k_rns_enter_ops(const KeyDev *_
 #pragma unroll
             for (int i = 0; i < L; ++i) x[i] = rns ? x[i] : m[i];
         }
-        __syncthreads();
-        store_words<S, G, 29>(out_pool + op.out_off + (half ? 0 : hl), x, hl, live, true, lds);
+        store_words<S, G, 29>(mid + (size_t)o * kMidWords + (half ? 0 : hl), x, hl, live, true, lds);
         lds_sync();
     }
 }
@@ -348,7 +350,8 @@ template <int S, int G>
 __global__ __launch_bounds__(64 * kIoWaves) void k_rns_leave_ops(const KeyDev *__restrict__ keys,
                                                                  const OpDesc *__restrict__ ops,
                                                                  const unsigned *__restrict__ list,
-                                                                 const unsigned *__restrict__ size, uint32_t *out_pool)
+                                                                 const unsigned *__restrict__ size,
+                                                                 const uint32_t *__restrict__ mid, uint32_t *out_pool)
 {
     using Ar = Arith<S, G, 29>;
     constexpr int L = S / G, NG = 64 / G;
@@ -361,18 +364,19 @@ __global__ __launch_bounds__(64 * kIoWaves) void k_rns_leave_ops(const KeyDev *_
         const bool live = at != kOrderHole;
         const uint64_t any = __ballot(live);
         if (any == 0) continue;
-        const OpDesc &op = ops[live ? at : list[first + (unsigned)__builtin_ctzll(any) / G]];
+        const unsigned o = live ? at : list[first + (unsigned)__builtin_ctzll(any) / G];
+        const OpDesc &op = ops[o];
         const KeyDev &k = keys[op.key_id];
         const int hl = k.hwords;
-        uint32_t *o = out_pool + op.out_off;
+        const uint32_t *m = mid + (size_t)o * kMidWords;
         uint32_t n[L], qn[L], A[L], mq[L], qv[L];
         Ar::load(n, k.p, hl, 0, live);
         Ar::load(qn, k.q, hl, 0, live);
-        Ar::load(mq, o, hl, 0, live);
-        Ar::load(A, o + hl, hl, 0, live);
+        Ar::load(mq, m, hl, 0, live);
+        Ar::load(A, m + hl, hl, 0, live);
         load_raw<S, G>(qv, k.cp[1].xr, live);                    // qinv * R mod p
         const uint32_t n0inv = Ar::n0inv(grp_bcast0<G>(n[0]) | 1u);
-        garner_store<S, G>(o, A, mq, qv, n, qn, n0inv, 2 * hl, live, true, lds);
+        garner_store<S, G>(out_pool + op.out_off, A, mq, qv, n, qn, n0inv, 2 * hl, live, true, lds);
         lds_sync();
     }
 }
@@ -423,15 +427,15 @@ hipError_t launch_rns_ops(const RnsOpsArgs &a, hipStream_t stream)
         return dim3((unsigned)(b < cap ? b : cap));
     };
     hipLaunchKernelGGL((k_rns_enter_ops<S, G, U>), blocks(ng * kIoWaves / 2), dim3(64 * kIoWaves), lds, stream, a.keys,
-                       a.ops, a.list, a.size, a.in_pool, a.out_pool);
+                       a.ops, a.list, a.size, a.in_pool, a.mid);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.entered && (e = hipEventRecord(a.entered, stream)) != hipSuccess) return e;
-    const RnsOpsSource src{a.keys, a.ops, a.list, a.size, a.out_pool, 0, ~0u, 0};
+    const RnsOpsSource src{a.keys, a.ops, a.list, a.size, a.mid, 0, ~0u, 0};
     e = rns_pow_bucket<U>(src, (a.most + 15) / 16, a.bulk, a.cus, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_rns_leave_ops<S, G>), blocks(ng * kIoWaves), dim3(64 * kIoWaves), lds, stream, a.keys, a.ops,
-                       a.list, a.size, a.out_pool);
+                       a.list, a.size, (const uint32_t *)a.mid, a.out_pool);
     return hipGetLastError();
 }
 

@@ -113,7 +113,7 @@ struct RnsOpsSource {
     const KeyDev *keys;
     const OpDesc *ops;
     const unsigned *list, *size;
-    uint32_t *out_pool;
+    uint32_t *mid;
     unsigned above, upto;
     unsigned skip;                      // tiles before the launch's first
     static constexpr bool kLoop = false;
@@ -129,14 +129,14 @@ struct RnsOpsSource {
         const unsigned at = idx < *size ? list[idx] : kOrderHole;
         RnsJob j;
         j.live = at != kOrderHole;
-        const OpDesc &op = ops[j.live ? at : list[first]];       // a tile's first entry is never a hole
-        const KeyDev &k = keys[op.key_id];
+        const unsigned o = j.live ? at : list[first];            // a tile's first entry is never a hole
+        const KeyDev &k = keys[ops[o].key_id];
         j.live = j.live && k.rns != 0;                           // (k_rns_enter_ops has done the others)
         const bool second = blockIdx.y != 0;
         j.n = second ? k.q : k.p;
         j.e = second ? k.dq : k.dp;
         j.words = k.hwords;
-        j.io = out_pool + op.out_off + (second ? 0 : k.hwords);
+        j.io = mid + (size_t)o * kMidWords + (second ? 0 : k.hwords);
         return j;
     }
 };
