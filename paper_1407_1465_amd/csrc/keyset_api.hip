@@ -442,7 +442,7 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
         // where the LDS holds them (see crt_pairs)
         const Instance *in = plan[t].inst;
         pairs[t] = kind == 1 && bulk && crt_lds_fits(in->S, in->G, in->B, plan[t].w, 2) ? 2 : 1;
-        rns[t] = kind == 1 && mid_bytes ? rns_ops_of(width, pkind) : nullptr;
+        rns[t] = kind == 1 && mid_bytes ? rns_ops_of(plan[t]) : nullptr;
         if (kind == 1 && round_runs) units.u[b] = rns[t] ? 16u : (unsigned)(64 / plan[t].inst->G);
     }
     const unsigned op_blocks = (unsigned)((nops + 255) / 256);

@@ -30,16 +30,19 @@ const Instance *find_instance(int i, int B, int G);
 // Any instance of class i in radix 2^B (for work whose speed does not matter).
 const Instance *any_instance(int i, int B);
 
+// One reading of a class's plan (another thread may set it at any time).
 struct Resolved {
     const Instance *inst;
     int w;
+    int cls;                          // class index
+    bool rns;                         // RNS exponentiation may take the instance's place
 };
 bool resolve(int limbs, int kind, Resolved *r);
-// RNS exponentiation of the CRT bucket whose halves have `hl` words at plan
-// `kind` (3 or 4), or nullptr; and whether a number of `words` words has no
+// RNS exponentiation of a CRT bucket whose halves run plan `r`, or nullptr;
+// and whether a number of `words` words has no
 // factor in common with base A of the configuration of width class i (true
 // where there is none).
-rns_ops_launcher rns_ops_of(int hl, int kind);
+rns_ops_launcher rns_ops_of(const Resolved &r);
 bool rns_coprime_host(int i, const uint32_t *n, int words);
 // rsa_ops_batch calls of at least this many operations take the kind-4 plan
 // for the CRT bucket of their widest class.

@@ -407,10 +407,10 @@ template <int U, int S, int G>
 hipError_t launch_rns_exp_on(const RnsExpArgs &a, int window, hipStream_t stream)
 {
     static_assert(S >= RnsTables<U>::LIMBS, "limbs of the configuration");
-    const size_t per = 64 / G * kIoWaves;
-    hipLaunchKernelGGL((k_rns_enter_exp<S, G, U>), dim3((unsigned)((a.count + per - 1) / per)), dim3(64 * kIoWaves),
-                       kIoWaves * lds_bytes_for(S, G, 29, window), stream, a.base, a.exp, a.mod, a.out,
-                       (unsigned long long)a.count, a.limbs, window, a.errs);
+    const size_t per = 64 / G * kIoWaves, lds = kIoWaves * lds_bytes_for(S, G, 29, window);
+    if (lds > kMaxGroupLds) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_rns_enter_exp<S, G, U>), dim3((unsigned)((a.count + per - 1) / per)), dim3(64 * kIoWaves), lds,
+                       stream, a.base, a.exp, a.mod, a.out, (unsigned long long)a.count, a.limbs, window, a.errs);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const RnsExpSource<false> src{a.mod, a.exp, a.out, (unsigned long long)a.count, a.limbs};

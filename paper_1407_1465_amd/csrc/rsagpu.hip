@@ -164,17 +164,10 @@ static_assert(sizeof(kRnsCrt) / sizeof(kRnsCrt[0]) == sizeof(kClasses) / sizeof(
 static const rns_exp_launcher kRnsExp[] = {nullptr,     nullptr,     nullptr,      nullptr, &rns_exp_u5, &rns_exp_u7,
                                            &rns_exp_u9, &rns_exp_u13, &rns_exp_u17, nullptr, nullptr};
 
-static bool default_plan(int kind, int i) { return g_plan[kind][i].load() == pack(kDefault[kind][i]); }
-
 static const rns_ops_launcher kRnsOps[] = {nullptr,     nullptr,     nullptr,      nullptr, &rns_ops_u5, &rns_ops_u7,
                                            &rns_ops_u9, &rns_ops_u13, &rns_ops_u17, nullptr, nullptr};
 
-rns_ops_launcher rns_ops_of(int hl, int kind)
-{
-    std::call_once(g_plan_once, init_plans);
-    const int i = class_index(hl);
-    return i >= 0 && default_plan(kind, i) ? kRnsOps[i] : nullptr;
-}
+rns_ops_launcher rns_ops_of(const Resolved &r) { return r.rns ? kRnsOps[r.cls] : nullptr; }
 
 #include "rns_primes.inc"
 
@@ -209,12 +202,11 @@ static const size_t kRnsTile = 16;            // integers of one RNS tile
 // The RNS path of a plain CRT call, or nullptr.  For 512-bit halves it holds
 // one tile per SIMD: beyond that the positional kernel is the faster one (16
 // keys, 8000 messages: 375 us against 661; 32768: 1479 against 1303).
-static rns_crt_launcher rns_crt_of(int hl, size_t count, int cus)
+static rns_crt_launcher rns_crt_of(const Resolved &r, size_t count, int cus)
 {
-    const int i = class_index(hl);
-    if (i < 0 || !default_plan(1, i)) return nullptr;
-    if (kClasses[i] <= 16 && 2 * ((count + kRnsTile - 1) / kRnsTile) > 4 * (size_t)cus) return nullptr;
-    return kRnsCrt[i];
+    if (!r.rns) return nullptr;
+    if (kClasses[r.cls] <= 16 && 2 * ((count + kRnsTile - 1) / kRnsTile) > 4 * (size_t)cus) return nullptr;
+    return kRnsCrt[r.cls];
 }
 
 // The RNS path of a plain exponentiation call, or nullptr.  The lines are
@@ -225,14 +217,13 @@ static rns_crt_launcher rns_crt_of(int hl, size_t count, int cus)
 // exponentiations 4731 us against 16532, but 16384 encryptions 191 against
 // 178).  In between any number: 16384 of 1536 bits 4130 us against 9567, short
 // ones 157 against 154; 65536 of 1024 bits 4333 against 6921.
-static rns_exp_launcher rns_exp_of(int limbs, size_t count, int cus)
+static rns_exp_launcher rns_exp_of(const Resolved &r, size_t count, int cus)
 {
-    const int i = class_index(limbs);
-    if (i < 0 || !default_plan(0, i)) return nullptr;
+    if (!r.rns) return nullptr;
     const size_t tiles = (count + kRnsTile - 1) / kRnsTile;
-    if (kClasses[i] <= 16 && tiles > 4 * (size_t)cus) return nullptr;
-    if (kClasses[i] > 48 && tiles > (size_t)cus) return nullptr;
-    return kRnsExp[i];
+    if (kClasses[r.cls] <= 16 && tiles > 4 * (size_t)cus) return nullptr;
+    if (kClasses[r.cls] > 48 && tiles > (size_t)cus) return nullptr;
+    return kRnsExp[r.cls];
 }
 
 // Slots of the processing order of an RNS call: the tiles of both halves may
@@ -254,9 +245,12 @@ bool resolve(int limbs, int kind, Resolved *r)
     std::call_once(g_plan_once, init_plans);
     const int i = class_index(limbs);
     if (i < 0) return false;
-    const Plan p = unpack(g_plan[kind][i].load());
+    const int v = g_plan[kind][i].load();
+    const Plan p = unpack(v);
     r->inst = find_instance(i, p.B, p.G);
     r->w = p.w;
+    r->cls = i;
+    r->rns = v == pack(kDefault[kind][i]);
     return r->inst != nullptr && (!crt_kind(kind) || (r->inst->crt && r->inst->ops_crt));
 }
 
@@ -330,7 +324,7 @@ extern "C" int rsa_modexp_batch(const uint32_t *base, const uint32_t *exp, const
     int cus = 1;
     const int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
-    if (const rns_exp_launcher rns = rns_exp_of(limbs, count, cus))
+    if (const rns_exp_launcher rns = rns_exp_of(r, count, cus))
         return status_of(rns(RnsExpArgs{base, exp, mod, out, count, limbs, cus, r.w, errs}, stream));
     return status_of(r.inst->modexp(base, exp, mod, out, count, limbs, r.w, errs, stream));
 }
@@ -378,7 +372,7 @@ extern "C" int rsa_decrypt_crt_batch(const uint32_t *c, const uint32_t *p, const
     int cus = 1;
     const int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
-    const rns_crt_launcher rns = rns_crt_of(limbs / 2, count, cus);
+    const rns_crt_launcher rns = rns_crt_of(r, count, cus);
     const size_t ng = rns ? kRnsTile : 64 / r.inst->G;
     // more than one wave's worth of messages: process them grouped by key
     size_t slots = count;
@@ -410,7 +404,7 @@ extern "C" int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p
     int cus = 1;
     const int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
-    const rns_crt_launcher rns = rns_crt_of(limbs / 2, count, cus);
+    const rns_crt_launcher rns = rns_crt_of(r, count, cus);
     const size_t ng = rns ? kRnsTile : 64 / r.inst->G;
     size_t slots = count;
     const unsigned *order = nullptr;
