@@ -777,11 +777,14 @@ def main():
                 swap = kind == 1 and L == sizes[0]
                 if swap:
                     p3, p4 = rsagpu.get_plan(L // 2, 3), rsagpu.get_plan(L // 2, 4)
+                    path3 = rsagpu.get_path(L // 2, 3)
                     rsagpu.set_plan(L // 2, 3, p4.radix_bits, p4.lanes_per_op, p4.window_bits)
+                    rsagpu.set_path(L // 2, 3, rsagpu.get_path(L // 2, 4))
                 sub = rsagpu.pack_ops(wl.kinds[idx], wl.key_ids[idx], wl.in_offs[idx], wl.in_offs[idx]).cuda()
                 ms_b, _ = timed(lambda: rsagpu.ops_batch(ks, sub, inp, out, ws, nops=len(idx)), 3, 1, torch)
                 if swap:
                     rsagpu.set_plan(L // 2, 3, p3.radix_bits, p3.lanes_per_op, p3.window_bits)
+                    rsagpu.set_path(L // 2, 3, path3)
                 alone["%d-bit %s" % (32 * L, "CRT" if kind else "encrypt")] = {"ops": int(idx.size), "ms": ms_b}
         line["buckets_alone_ms"] = alone
         line.update(metric="mixed-size RSA ops/sec (1024-4096-bit, half CRT decrypt) on 1 GPU", unit="ops/s",

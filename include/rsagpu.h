@@ -135,12 +135,18 @@ int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p, const uin
 /*
  * Exponentiations modulo 13 to 64 words (rsa_modexp_batch, and the halves of
  * CRT decryptions, also in rsa_ops_batch) run in a residue number system on
- * the matrix cores
- * where their width's plan is the default one, except where a batch is so
- * large that the positional kernel is faster; exponents of at most 64 bits,
- * encryptions and every other width run on the positional kernels, which the plans below
- * describe.  A plan that is not the default (rsa_set_plan) is obeyed for
- * every exponentiation of its width.  Results do not depend on it.
+ * the matrix cores, with two exceptions by the size of a plain call: 13 to 16
+ * words above 64 elements (CRT: 32 messages) per compute unit, where the
+ * positional kernel is the faster one, and rsa_modexp_batch of 49 to 64 words
+ * above 16 elements per compute unit (4096 on 256), where calls of public
+ * exponents, which the host cannot tell apart, would pay for it (2048-bit
+ * private exponents: 4096 take 2.2 ms in one call, 4097 take 14.2 ms, so larger
+ * batches of them go faster in calls of 4096).  Exponents of at most 64 bits,
+ * encryptions and
+ * every other width run on the positional kernels, which the plans below
+ * describe.  A plan set with rsa_set_plan is obeyed for every exponentiation
+ * of its width and kind, the default one too (rsa_set_path, rsa_get_path).
+ * Results do not depend on it.
  *
  * Execution plan used for a limb width: the limb radix the kernel computes
  * in (radix_bits = 32, or 29 for the reduced-radix kernels whose 64-bit
@@ -176,22 +182,51 @@ int rsa_get_plan(int limbs, int kind, rsa_plan *plan);
 
 /*
  * Overrides the plan of the width class that `limbs` maps to (kind as in
- * rsa_get_plan): (radix_bits, lanes_per_op) must name a compiled kernel
- * instance for that class, 2 <= window_bits <= 7, and the plan's LDS
+ * rsa_get_plan) and sets its path to RSA_PATH_POSITIONAL: (radix_bits,
+ * lanes_per_op) must name a compiled kernel instance for that class, 2 <= window_bits <= 7, and the plan's LDS
  * (lds_bytes of rsa_get_plan) must fit 64 KiB; for a CRT kind (1, 3, 4) the
  * workgroup's LDS (2 or 4 times lds_bytes, as above, plus 16 bytes) must
  * also fit the 160 KiB a workgroup may hold.  All three zero restores the
- * default.
+ * default, and the path RSA_PATH_AUTO.
  * Used by the tuner; affects calls issued afterwards from any thread.
  * Pure host call.
  */
 int rsa_set_plan(int limbs, int kind, int radix_bits, int lanes_per_op, int window_bits);
 
 /*
+ * Which kernels the exponentiations of a width class and kind (as in
+ * rsa_get_plan) run on: RSA_PATH_AUTO, the default, RNS where it serves the
+ * call (see above) and the plan's positional kernel elsewhere;
+ * RSA_PATH_POSITIONAL, the plan's positional kernel always.  The plan stays as
+ * it is.  Affects calls issued afterwards from any thread.  Pure host call.
+ */
+typedef enum {
+    RSA_PATH_AUTO = 0,
+    RSA_PATH_POSITIONAL = 1,
+    RSA_PATH_RNS = 2
+} rsa_path;
+
+int rsa_set_path(int limbs, int kind, int path);
+
+/*
+ * The path that a call of `count` elements or operations takes on the current
+ * device, RSA_PATH_POSITIONAL or RSA_PATH_RNS (exponents longer than 64 bits;
+ * for kinds 3 and 4 the bucket's); with count 0 the setting, RSA_PATH_AUTO or
+ * RSA_PATH_POSITIONAL.  Host query (kinds 0 and 1 with count > 0 look up the
+ * device's compute units).
+ */
+int rsa_get_path(int limbs, int kind, size_t count, int *path);
+
+/*
  * Autotuner: for the width class of `limbs` and plan `kind` (as in
  * rsa_get_plan), times every compiled kernel instance of the class at every
- * window width that fits, on `count` synthetic operands laid out as the
- * workloads have them, and installs the fastest plan (rsa_set_plan):
+ * window width that fits, and the RNS kernels where they serve the call, on
+ * `count` synthetic operands laid out as the workloads have them, and installs
+ * the fastest: the default plan and RSA_PATH_AUTO if that is RNS, else the
+ * fastest plan as rsa_set_plan does.  Where RNS does not serve such a call, or
+ * leaves it to its positional part (kind 0 with at most 64 exponent bits), the
+ * path becomes RSA_PATH_AUTO beside the plan: the class's calls that RNS does
+ * serve keep it.
  *   kind 0: rsa_modexp_batch of `limbs`-word operands under one modulus and
  *           one exp_bits-bit exponent (one key's messages);
  *   kind 1: rsa_decrypt_crt_batch of `limbs`-word moduli, 16 keys

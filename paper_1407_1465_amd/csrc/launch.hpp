@@ -116,6 +116,10 @@ inline bool crt_lds_fits(int S, int G, int B, int w, int pairs)
 
 
 // RNS exponentiation (rns_kernels.hpp): the launchers of one configuration.
+// Exponents of up to this many bits (public exponents) are exponentiated
+// positionally by k_rns_enter_exp: the way into and out of RNS costs about as
+// much as their products.
+constexpr int kRnsMinBits = 64;
 struct RnsCrtArgs {
     const uint32_t *c, *p, *q, *dp, *dq, *qinv;
     const unsigned *order;            // `slots` slots, or nullptr: the given order

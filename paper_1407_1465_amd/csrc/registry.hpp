@@ -38,6 +38,13 @@ struct Resolved {
     bool rns;                         // RNS exponentiation may take the instance's place
 };
 bool resolve(int limbs, int kind, Resolved *r);
+// The plan of class i at `kind` as one value, kept and put back by the tuner;
+// the default one; and whether a call of `count` elements would run in RNS
+// there but for a plan set by the caller (on a device of `cus` compute units).
+int plan_value(int i, int kind);
+void install_plan(int i, int kind, int value);
+void default_plan(int i, int kind);
+bool rns_runs(int i, int kind, size_t count, int cus);
 // RNS exponentiation of a CRT bucket whose halves run plan `r`, or nullptr;
 // and whether a number of `words` words has no
 // factor in common with base A of the configuration of width class i (true

@@ -16,11 +16,6 @@ struct RnsJob {
     bool live;                 // false: no element (the pointers are another's)
 };
 
-// Exponents of up to this many bits (public exponents) are exponentiated
-// positionally by k_rns_enter_exp: the way into and out of RNS costs about as
-// much as their products.
-constexpr int kRnsMinBits = 64;
-
 // Limbs per reduction of a sum of limb * constant products: at most 7 keep
 // 7 * 2^59 + 2^44 below 2^63 and the reduced word below 0.95 * 2^31.
 template <int S>

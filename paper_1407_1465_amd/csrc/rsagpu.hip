@@ -109,9 +109,12 @@ static const Plan kDefault[kKinds][kNumClasses] = {
 };
 
 static int pack(const Plan &p) { return p.B << 16 | p.G << 8 | p.w; }
-static Plan unpack(int v) { return Plan{v >> 16, (v >> 8) & 0xFF, v & 0xFF}; }
+static Plan unpack(int v) { return Plan{(v >> 16) & 0xFF, (v >> 8) & 0xFF, v & 0xFF}; }
 
-// Current plans; overridable with rsa_set_plan.
+// Current plans; overridable with rsa_set_plan.  A plan describes a positional
+// kernel; with kPositional that kernel runs every call of the class, otherwise
+// those that RNS exponentiation does not take (rsa_set_path).
+static const int kPositional = 1 << 30;
 static std::atomic<int> g_plan[kKinds][kNumClasses];
 static std::once_flag g_plan_once;
 
@@ -153,10 +156,18 @@ const Instance *any_instance(int i, int B)
     return nullptr;
 }
 
+int plan_value(int i, int kind)
+{
+    std::call_once(g_plan_once, init_plans);
+    return g_plan[kind][i].load();
+}
+void install_plan(int i, int kind, int value) { g_plan[kind][i].store(value); }
+void default_plan(int i, int kind) { install_plan(i, kind, pack(kDefault[kind][i])); }
+
 // RNS exponentiation (rns_kernels.hpp) of CRT halves, by width class; null
-// where there is none.  It takes the place of the positional kernel where the
-// class runs its default plan: a plan set by the caller names a positional
-// kernel and is obeyed.
+// where there is none.  It takes the place of the positional kernel unless the
+// class's plan was set by the caller, which names a positional kernel and is
+// obeyed (kPositional).
 static const rns_crt_launcher kRnsCrt[] = {nullptr,     nullptr,     nullptr,      nullptr, &rns_crt_u5, &rns_crt_u7,
                                            &rns_crt_u9, &rns_crt_u13, &rns_crt_u17, nullptr, nullptr};
 static_assert(sizeof(kRnsCrt) / sizeof(kRnsCrt[0]) == sizeof(kClasses) / sizeof(kClasses[0]), "one entry per class");
@@ -240,6 +251,17 @@ static size_t rns_order_slots(size_t count, int cus)
 
 static bool crt_kind(int kind) { return kind == 1 || kind == 3 || kind == 4; }
 
+bool rns_runs(int i, int kind, size_t count, int cus)
+{
+    const Resolved r{nullptr, 0, i, true};
+    switch (kind) {
+    case 0: return rns_exp_of(r, count, cus) != nullptr;
+    case 1: return rns_crt_of(r, count, cus) != nullptr;
+    case 2: return false;
+    default: return kRnsOps[i] != nullptr;
+    }
+}
+
 bool resolve(int limbs, int kind, Resolved *r)
 {
     std::call_once(g_plan_once, init_plans);
@@ -250,7 +272,7 @@ bool resolve(int limbs, int kind, Resolved *r)
     r->inst = find_instance(i, p.B, p.G);
     r->w = p.w;
     r->cls = i;
-    r->rns = v == pack(kDefault[kind][i]);
+    r->rns = !(v & kPositional);
     return r->inst != nullptr && (!crt_kind(kind) || (r->inst->crt && r->inst->ops_crt));
 }
 
@@ -325,7 +347,7 @@ extern "C" int rsa_modexp_batch(const uint32_t *base, const uint32_t *exp, const
     const int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
     if (const rns_exp_launcher rns = rns_exp_of(r, count, cus))
-        return status_of(rns(RnsExpArgs{base, exp, mod, out, count, limbs, cus, r.w, errs}, stream));
+        return status_of(rns(RnsExpArgs{base, exp, mod, out, count, limbs, cus, kDefault[0][r.cls].w, errs}, stream));
     return status_of(r.inst->modexp(base, exp, mod, out, count, limbs, r.w, errs, stream));
 }
 
@@ -451,7 +473,38 @@ extern "C" int rsa_set_plan(int limbs, int kind, int radix_bits, int lanes_per_o
     if (lds_bytes_for(in->S, in->G, in->B, window_bits) > 64 * 1024) return RSA_EINVAL;
     if (crt_kind(kind) && !crt_lds_fits(in->S, in->G, in->B, window_bits, kind == 3 ? 1 : crt_pairs(in->G)))
         return RSA_EINVAL;
-    g_plan[kind][i].store(pack(Plan{radix_bits, lanes_per_op, window_bits}));
+    install_plan(i, kind, pack(Plan{radix_bits, lanes_per_op, window_bits}) | kPositional);
+    return RSA_OK;
+}
+
+extern "C" int rsa_set_path(int limbs, int kind, int path)
+{
+    if (kind < 0 || kind >= kKinds || (path != RSA_PATH_AUTO && path != RSA_PATH_POSITIONAL)) return RSA_EINVAL;
+    if (limbs < 1 || limbs > RSA_MAX_LIMBS) return RSA_ELIMBS;
+    Resolved r;
+    if (!resolve(limbs, kind, &r)) return RSA_ELIMBS;
+    if (path == RSA_PATH_POSITIONAL) g_plan[kind][r.cls].fetch_or(kPositional);
+    else g_plan[kind][r.cls].fetch_and(~kPositional);
+    return RSA_OK;
+}
+
+extern "C" int rsa_get_path(int limbs, int kind, size_t count, int *path)
+{
+    if (!path || kind < 0 || kind >= kKinds) return RSA_EINVAL;
+    if (limbs < 1 || limbs > RSA_MAX_LIMBS) return RSA_ELIMBS;
+    Resolved r;
+    if (!resolve(limbs, kind, &r)) return RSA_ELIMBS;
+    if (count == 0) {
+        *path = r.rns ? RSA_PATH_AUTO : RSA_PATH_POSITIONAL;
+        return RSA_OK;
+    }
+    int cus = 1;
+    if (kind < 2) {                                          // by the device's size
+        unsigned long long *errs = nullptr;
+        const int st = device_state(&errs, &cus);
+        if (st != RSA_OK) return st;
+    }
+    *path = r.rns && rns_runs(r.cls, kind, count, cus) ? RSA_PATH_RNS : RSA_PATH_POSITIONAL;
     return RSA_OK;
 }
 

@@ -1,6 +1,6 @@
 // Plan autotuner: times every compiled kernel instance of a width class at
-// every window that fits, on synthetic operands of the caller's batch size,
-// and installs the fastest plan.
+// every window that fits, and the RNS kernels where they take the call, on
+// synthetic operands of the caller's batch size, and installs the fastest.
 #include "../../include/rsagpu.h"
 #include "registry.hpp"
 
@@ -149,7 +149,8 @@ extern "C" int rsa_autotune(int limbs, int kind, int exp_bits, size_t count, hip
     const int cls = class_index(width);
     if (cls < 0) return RSA_ELIMBS;
     unsigned long long *errs = nullptr;
-    int st = device_state(&errs);
+    int cus = 1;
+    int st = device_state(&errs, &cus);
     if (st != RSA_OK) return st;
 
     // synthetic operands (freed before returning)
@@ -235,11 +236,27 @@ extern "C" int rsa_autotune(int limbs, int kind, int exp_bits, size_t count, hip
     // a CRT bucket takes plan kind 3 or 4 by the batch's size and rank, so
     // both are set to the candidate while a CRT kind is timed
     const int twin = kind == 3 ? 4 : (kind == 4 ? 3 : -1);
-    rsa_plan twin_saved{};
-    if (twin >= 0 && (st = rsa_get_plan(width, twin, &twin_saved)) != RSA_OK) { release(); return st; }
+    const int twin_saved = twin >= 0 ? plan_value(cls, twin) : 0;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) { release(); return RSA_EHIP; }
-    float best_ms = -1.0f;
+    auto run = [&]() {
+        if (kind == 0) return rsa_modexp_batch(a, b, m, out, count, limbs, stream);
+        if (kind == 1) return rsa_decrypt_crt_batch(a, p, q, dp, dq, qi, out, count, limbs, stream);
+        return rsa_ops_batch(ks, static_cast<const rsa_op *>(ops), count, a, count * limbs, out, count * limbs, ws,
+                             ws_bytes, stream);
+    };
+    // Where RNS takes calls like this one, its kernels are a candidate (they
+    // need no plan), and a plan that beats them is set as a caller's is.  Not
+    // so where it does not, or where the exponents are short: RNS then does
+    // nothing for the call, the class's calls that it does serve keep it
+    // whatever plan is found, and the plan is for the others.
+    const bool rns = rns_runs(cls, kind, count, cus) && !(kind == 0 && exp_bits <= kRnsMinBits);
+    float rns_ms = -1.0f, best_ms = -1.0f;
+    if (rns) {
+        default_plan(cls, kind);
+        if (twin >= 0) default_plan(cls, twin);
+        rns_ms = time_runs(run, e0, e1, stream);
+    }
     int bB = 0, bG = 0, bw = 0;
     for (int B : {32, 29}) {
         for (int G : {1, 2, 4, 8, 16}) {
@@ -248,12 +265,6 @@ extern "C" int rsa_autotune(int limbs, int kind, int exp_bits, size_t count, hip
             for (int w = 2; w <= 6; ++w) {
                 if (rsa_set_plan(width, kind, B, G, w) != RSA_OK) continue;
                 if (twin >= 0 && rsa_set_plan(width, twin, B, G, w) != RSA_OK) continue;
-                auto run = [&]() {
-                    if (kind == 0) return rsa_modexp_batch(a, b, m, out, count, limbs, stream);
-                    if (kind == 1) return rsa_decrypt_crt_batch(a, p, q, dp, dq, qi, out, count, limbs, stream);
-                    return rsa_ops_batch(ks, static_cast<const rsa_op *>(ops), count, a, count * limbs, out,
-                                         count * limbs, ws, ws_bytes, stream);
-                };
                 const float ms = time_runs(run, e0, e1, stream);
                 if (ms < 0.0f) continue;
                 if (best_ms < 0.0f || ms < best_ms) { best_ms = ms; bB = B; bG = G; bw = w; }
@@ -263,13 +274,17 @@ extern "C" int rsa_autotune(int limbs, int kind, int exp_bits, size_t count, hip
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     release();
-    if (twin >= 0)
-        (void)rsa_set_plan(width, twin, twin_saved.radix_bits, twin_saved.lanes_per_op, twin_saved.window_bits);
-    if (best_ms < 0.0f) {
-        (void)rsa_set_plan(width, kind, 0, 0, 0);
+    if (twin >= 0) install_plan(cls, twin, twin_saved);
+    if (best_ms < 0.0f && rns_ms < 0.0f) {
+        default_plan(cls, kind);
         return RSA_EHIP;
     }
-    st = rsa_set_plan(width, kind, bB, bG, bw);
+    if (rns_ms >= 0.0f && (best_ms < 0.0f || rns_ms <= best_ms)) {
+        default_plan(cls, kind);
+    } else {
+        st = rsa_set_plan(width, kind, bB, bG, bw);
+        if (st == RSA_OK && !rns) st = rsa_set_path(width, kind, RSA_PATH_AUTO);
+    }
     if (st == RSA_OK && best) st = rsa_get_plan(width, kind, best);
     return st;
 }

@@ -48,6 +48,10 @@ _lib.rsa_get_plan.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.POINTER(_Plan)]
 _lib.rsa_get_plan.restype = ctypes.c_int
 _lib.rsa_set_plan.argtypes = [ctypes.c_int] * 5
 _lib.rsa_set_plan.restype = ctypes.c_int
+_lib.rsa_set_path.argtypes = [ctypes.c_int] * 3
+_lib.rsa_set_path.restype = ctypes.c_int
+_lib.rsa_get_path.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)]
+_lib.rsa_get_path.restype = ctypes.c_int
 _lib.rsa_autotune.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_size_t, _P, ctypes.POINTER(_Plan)]
 _lib.rsa_autotune.restype = ctypes.c_int
 _lib.rsa_init.argtypes = []
@@ -69,9 +73,14 @@ _lib.rsa_keyset_set_forks.argtypes = [_P, ctypes.c_int]
 _lib.rsa_keyset_set_forks.restype = ctypes.c_int
 
 # exported symbols, in the order include/rsagpu.h declares them
-EXPORTS = ("rsa_modexp_batch", "rsa_decrypt_crt_batch", "rsa_decrypt_crt_batch_static", "rsa_get_plan", "rsa_set_plan", "rsa_autotune", "rsa_init",
+EXPORTS = ("rsa_modexp_batch", "rsa_decrypt_crt_batch", "rsa_decrypt_crt_batch_static", "rsa_get_plan", "rsa_set_plan",
+           "rsa_set_path", "rsa_get_path", "rsa_autotune", "rsa_init",
            "rsa_keyset_create", "rsa_keyset_add", "rsa_keyset_destroy", "rsa_ops_workspace_size",
            "rsa_ops_batch", "rsa_keyset_set_forks", "rsa_device_errors", "rsa_status_str", "rsa_version")
+
+PATH_AUTO = 0
+PATH_POSITIONAL = 1
+PATH_RNS = 2
 
 OP_ENCRYPT = 0
 OP_DECRYPT_CRT = 1
@@ -105,13 +114,28 @@ def get_plan(limbs: int, kind: int = 0) -> Plan:
 
 
 def set_plan(limbs: int, kind: int, radix_bits: int, lanes_per_op: int, window_bits: int) -> None:
-    """Override the plan of a limb width (all zero restores the default)."""
+    """Override the plan of a limb width, which its calls then run on (all
+    zero restores the default)."""
     _check(_lib.rsa_set_plan(limbs, kind, radix_bits, lanes_per_op, window_bits), "rsa_set_plan")
+
+
+def set_path(limbs: int, kind: int, path: int) -> None:
+    """PATH_AUTO: RNS where it serves a call, else the plan; PATH_POSITIONAL: the plan."""
+    _check(_lib.rsa_set_path(limbs, kind, path), "rsa_set_path")
+
+
+def get_path(limbs: int, kind: int, count: int = 0) -> int:
+    """The path a call of `count` elements takes (PATH_POSITIONAL or PATH_RNS);
+    with no count the setting (PATH_AUTO or PATH_POSITIONAL)."""
+    p = ctypes.c_int(-1)
+    _check(_lib.rsa_get_path(limbs, kind, count, ctypes.byref(p)), "rsa_get_path")
+    return p.value
 
 
 def autotune(limbs: int, kind: int, exp_bits: int, count: int,
              stream: Optional[torch.cuda.Stream] = None) -> Plan:
-    """Times every kernel instance / window for the class and installs the fastest."""
+    """Times every kernel instance / window for the class, and RNS where it
+    serves the call, and installs the fastest."""
     p = _Plan()
     _check(_lib.rsa_autotune(limbs, kind, exp_bits, count, _stream_handle(stream), ctypes.byref(p)), "rsa_autotune")
     return Plan(p.radix_bits, p.padded_limbs, p.lanes_per_op, p.limbs_per_lane, p.window_bits, p.lds_bytes)

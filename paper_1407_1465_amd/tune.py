@@ -2,11 +2,13 @@
 
 `tune(limbs, kind, exp_bits, count)` runs the library's autotuner
 (rsa_autotune: every compiled kernel instance of the width class at every
-window that fits, timed on synthetic operands of the given batch size: plain
-calls for kinds 0 and 1, rsa_ops_batch on a synthetic keyset for kinds 2 to
-4) and records the winner in a JSON cache; `apply_cached()` re-installs
-cached plans with rsa_set_plan so later processes skip the search.  Entries
-are keyed by the GPU architecture, the operand width in words, the kind, the
+window that fits, and the RNS kernels where they serve the call, timed on
+synthetic operands of the given batch size: plain calls for kinds 0 and 1,
+rsa_ops_batch on a synthetic keyset for kinds 2 to 4) and records the winner,
+plan and path, in a JSON cache; `apply_cached()` re-installs cached entries so
+later processes skip the search.  An entry without a path, of a search among
+the positional kernels alone, leaves RNS the calls it serves.  Entries are
+keyed by the GPU architecture, the operand width in words, the kind, the
 exponent length and the batch size rounded up to a power of two.
 
 `tune_batch(run, slots)` tunes the plans of a whole rsa_ops_batch call
@@ -68,18 +70,23 @@ def save(cache: Dict[str, dict]) -> None:
     os.replace(tmp, path)
 
 
+def _install(width: int, kind: int, entry: dict) -> None:
+    rsagpu.set_plan(width, kind, entry["radix_bits"], entry["lanes_per_op"], entry["window_bits"])
+    rsagpu.set_path(width, kind, entry.get("path", rsagpu.PATH_AUTO))
+
+
 def tune(limbs: int, kind: int, exp_bits: int, count: int, use_cache: bool = True) -> rsagpu.Plan:
     """Best plan for (limbs, kind, exp_bits, count), installed in the library."""
     cache = load()
     key = _key(limbs, kind, exp_bits, count)
     width = plan_width(limbs, kind)
     if use_cache and key in cache:
-        e = cache[key]
-        rsagpu.set_plan(width, kind, e["radix_bits"], e["lanes_per_op"], e["window_bits"])
+        _install(width, kind, cache[key])
         return rsagpu.get_plan(width, kind)
     plan = rsagpu.autotune(limbs, kind, exp_bits, count)
     cache[key] = {"radix_bits": plan.radix_bits, "lanes_per_op": plan.lanes_per_op,
-                  "window_bits": plan.window_bits, "padded_limbs": plan.padded_limbs}
+                  "window_bits": plan.window_bits, "padded_limbs": plan.padded_limbs,
+                  "path": rsagpu.get_path(width, kind)}
     save(cache)
     return plan
 
@@ -94,7 +101,7 @@ def apply_cached(arch: Optional[str] = None) -> int:
             continue
         limbs, kind = int(parts[1][1:]), int(parts[2][1:])
         width = plan_width(limbs, kind)
-        rsagpu.set_plan(width, kind, e["radix_bits"], e["lanes_per_op"], e["window_bits"])
+        _install(width, kind, e)
         n += 1
     return n
 
@@ -104,7 +111,7 @@ def candidate_plans(width: int, kind: int):
     width class of `width` and plan `kind` (the current plan is restored;
     none where the class has no plan of that kind)."""
     try:
-        cur = rsagpu.get_plan(width, kind)
+        cur, path = rsagpu.get_plan(width, kind), rsagpu.get_path(width, kind)
     except rsagpu.RSAError:
         return []
     out = []
@@ -117,6 +124,7 @@ def candidate_plans(width: int, kind: int):
                     continue
                 out.append((radix, lanes, w))
     rsagpu.set_plan(width, kind, cur.radix_bits, cur.lanes_per_op, cur.window_bits)
+    rsagpu.set_path(width, kind, path)
     return out
 
 
@@ -124,7 +132,9 @@ def tune_batch(run, slots, reps: int = 3, passes: int = 1, tolerance: float = 0.
                timer=None, confirm: int = 5):
     """Coordinate descent over the plans of `slots` [(width, kind), ...] for
     the batch that run() enqueues on torch's current stream: each candidate
-    is installed and the batch timed (one warm-up, then `reps` runs between
+    (a plan, which runs positionally; the slot's starting plan and path; and,
+    where that is RNS, the starting plan positionally, given as (radix, lanes,
+    window, "positional")) is installed and the batch timed (one warm-up, then `reps` runs between
     HIP events); a candidate replaces the slot's plan when it is faster by
     more than `tolerance` in two timings in a row (one lucky timing does not
     move the descent).  `knobs` [(name, values, apply)] are further settings
@@ -153,14 +163,26 @@ def tune_batch(run, slots, reps: int = 3, passes: int = 1, tolerance: float = 0.
         p = rsagpu.get_plan(width, kind)
         return (p.radix_bits, p.lanes_per_op, p.window_bits)
 
+    def put(slot, value):
+        rsagpu.set_plan(*slot, *value[:3])
+        if value == start[slot]:
+            rsagpu.set_path(*slot, path[slot])
+
     def install(cfg):
         for key, value in cfg.items():
             if isinstance(key, tuple):
-                rsagpu.set_plan(key[0], key[1], *value)
+                put(key, value)
         for name, _, apply in knobs:
             apply(cfg[name])
 
+    def candidates(slot):
+        yield from candidate_plans(*slot)
+        if path[slot] == rsagpu.PATH_AUTO and slot[1] in CRT_KINDS[1:] and \
+                rsagpu.get_path(*slot, 1) == rsagpu.PATH_RNS:
+            yield start[slot] + ("positional",)
+
     start = {(w, k): plan_of(w, k) for w, k in slots}
+    path = {(w, k): rsagpu.get_path(w, k) for w, k in slots}
     for name, values, _ in knobs:
         start[name] = values[0]
 
@@ -172,16 +194,16 @@ def tune_batch(run, slots, reps: int = 3, passes: int = 1, tolerance: float = 0.
     for _ in range(passes):
         for width, kind in slots:
             cur = chosen[(width, kind)]
-            for cand in candidate_plans(width, kind):
+            for cand in list(candidates((width, kind))):
                 if cand == cur:
                     continue
-                rsagpu.set_plan(width, kind, *cand)
+                put((width, kind), cand)
                 ms = timer()
                 if better(ms, best):
                     ms2 = timer()
                     if better(ms2, best):
                         best, cur = max(ms, ms2), cand
-            rsagpu.set_plan(width, kind, *cur)
+            put((width, kind), cur)
             chosen[(width, kind)] = cur
         for name, values, apply in knobs:
             cur = chosen[name]
