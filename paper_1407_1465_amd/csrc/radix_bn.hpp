@@ -64,6 +64,25 @@ __device__ __forceinline__ void rload(uint32_t (&x)[S / G], const uint32_t *p, i
     }
 }
 
+// The same with a load for each limb and word, which leaves the compiler freer
+// in the code around it: for the kernels whose loads are a small part.
+template <int S, int G, int B>
+__device__ __forceinline__ void rload_words(uint32_t (&x)[S / G], const uint32_t *p, int nwords, int bitoff,
+                                            bool live)
+{
+    constexpr int L = S / G;
+    const int r = grp_lane<G>();
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+        const int pos = bitoff + B * (r * L + k);
+        const int w = pos >> 5, sh = pos & 31;
+        const uint32_t lo = (live && w < nwords) ? p[w] : 0u;
+        const uint32_t hi = (live && w + 1 < nwords) ? p[w + 1] : 0u;
+        const uint64_t v = (((uint64_t)hi << 32) | lo) >> sh;
+        x[k] = (uint32_t)v & Radix<B>::MASK;
+    }
+}
+
 // Word k (32 bits) of an integer held as `nlimbs` B-bit limbs at q[0 ..].
 template <int B>
 __device__ __forceinline__ uint32_t rword(const uint32_t *q, int nlimbs, int k)
