@@ -249,7 +249,13 @@ __device__ __forceinline__ void mont_sqr(uint32_t (&A)[S / G], uint32_t *abuf, c
 // of that ladder are register products, lazy and symmetric between two
 // squarings (2048-bit e = 65537 encryptions ~2% faster; in the CRT kernel
 // the same change cost the exponentiation more than the set-up saved).
-template <int S, int G, int B, bool REG_LADDER = false>
+// MOVES (k_rns_enter_exp): one goes up by moves while more than 6 bits are left
+// in any lane group, not by two moves and then doublings: moduli shorter than
+// the limbs hold by up to 28 bits a move (the narrow groups' limbs are more than
+// their class's).  e = 65537, 4096 elements, us: 13 words 59 -> 36, 15 words 43
+// -> 35, 33 words 214 -> 105, 49 words 272 -> 98; 16 words 34.6 -> 34.0, 24 and
+// 32 words equal.  (k_modexp and k_crt keep the doublings.)
+template <int S, int G, int B, bool REG_LADDER = false, bool MOVES = false>
 __device__ __forceinline__ void mont_setup(uint32_t (&one)[S / G], uint32_t (&r2)[S / G],
                                            const uint32_t (&n)[S / G], uint32_t n0inv, bool valid,
                                            uint32_t *abuf)
@@ -272,8 +278,7 @@ __device__ __forceinline__ void mont_setup(uint32_t (&one)[S / G], uint32_t (&r2
     if constexpr (B < 32) {
         const double rn = 1.0 / rgrp_scaled<S, G, B>(n, 0u, (int)bl);
         uint32_t left = nup;
-#pragma unroll
-        for (int step = 0; step < 2; ++step) {
+        auto move = [&]() {
             const uint32_t c = left < B - 1 ? left : (uint32_t)(B - 1);
             uint32_t y[L];
 #pragma unroll
@@ -282,6 +287,12 @@ __device__ __forceinline__ void mont_setup(uint32_t (&one)[S / G], uint32_t (&r2
 #pragma unroll
             for (int k = 0; k < L; ++k) one[k] = c ? y[k] : one[k];
             left -= c;
+        };
+#pragma unroll
+        for (int step = 0; step < 2; ++step) move();
+        if constexpr (MOVES) {
+#pragma unroll 1
+            while (wave_max(left) > 6u) move();
         }
         const uint32_t maxd = wave_max(left);
         for (uint32_t t = 0; t < maxd; ++t) {

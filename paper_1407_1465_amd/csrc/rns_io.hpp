@@ -192,7 +192,7 @@ __global__ __launch_bounds__(64 * kIoWaves) RSAGPU_EXP_OCC(S / G) void k_rns_ent
     const bool valid = live && (n0 & 1u) && bl > 1;
     const uint32_t n0inv = Ar::n0inv(n0 | 1u);
     uint32_t one[L], r2[L], xt[L], A[L];
-    mont_setup<S, G, 29, true>(one, r2, n, n0inv, valid, lds);
+    mont_setup<S, G, 29, true, true>(one, r2, n, n0inv, valid, lds);
     mont_mul_reg<S, G, 29>(xt, x, r2, lds, n, n0inv);
     const bool wide = valid && grp_any<G>(upper != 0u);
     bool rns = false;
