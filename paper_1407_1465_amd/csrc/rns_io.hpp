@@ -441,6 +441,9 @@ hipError_t launch_rns_ops(const RnsOpsArgs &a, hipStream_t stream)
 
 // Narrow groups (S2 limbs on G2 lanes: a shorter chain of instructions per
 // product, more of them in all) where the waves they take have a SIMD each.
+// Plain exponentiation of 24 words, e = 65537, 64 .. 4096 elements: 43.5 .. 44.7
+// us on 28 limbs and 4 lanes, the idle k_rns_pow included, 35.0 .. 36.8 on 32
+// and 16 (k_modexp alone 42.7 .. 43.3).
 template <int U, int S, int G, int S2, int G2>
 hipError_t launch_rns_crt(const RnsCrtArgs &a, hipStream_t stream)
 {
