@@ -402,12 +402,12 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     // Bucket order and plans.  The CRT buckets of the widest classes are the
     // longest (their operations are long dependency chains that a bucket's
     // waves cannot shorten), so each of them gets a keyset stream of its own;
-    // the remaining buckets (narrower CRT classes, then all encryptions,
-    // widest first) follow each other on the caller's stream, beside them,
-    // which then waits for the keyset streams.  The widest CRT bucket's
-    // waves also raise their issue priority: every call ends with its
-    // operations, whose chains are the longest, so on a SIMD shared with other
-    // buckets' waves they issue first.
+    // the remaining buckets follow each other on the caller's stream, beside
+    // them, which then waits for the keyset streams: narrower CRT buckets,
+    // then all encryptions, widest first, and in a bulk batch the encryptions
+    // first.  A widest CRT bucket on a positional plan also raises its waves'
+    // issue priority, since the call then ends with its operations (RNS
+    // buckets have no priority).
     // In a bulk batch, whose buckets fill the chip, the forked buckets and then
     // the caller's stream start one after the other, widest first, each once
     // the tiles of the one before may be placed: a wide bucket's workgroups
@@ -417,6 +417,16 @@ extern "C" int rsa_ops_batch(rsa_keyset *ks, const rsa_op *ops, size_t nops, con
     // ms with the forks started together, 5.1 in turn; a smaller batch does
     // not fill the chip and would only wait).  The CRT buckets beyond the
     // streams follow the encryptions there (before them: 5.3 ms).
+    // Which buckets are empty only the device knows, so a bulk batch of
+    // encryptions alone waits its turn as well: 16384 of them, us, with and
+    // without the forks, 255 and 226 under 1024-bit keys, 311-333 and 282 under
+    // 2048-bit, 651 and 630 under 3072-bit, 597 and 570 under 4096-bit, 780 and
+    // 672 under all four (positional CRT buckets, which start together: 244,
+    // 308, 634, 589, 797 with the forks).  rsa_keyset_set_forks(0) is for such
+    // callers.
+    // Not waiting for the last fork cost batches with decryptions more (2048-
+    // and 4096-bit keys, half decryptions, 16384: 6.2 -> 7.5 ms), and so did
+    // encryptions launched a second time ahead of the wait (32768: 967 -> 1006).
     const bool bulk = nops >= kBulkOps;
     int order[kMaxBuckets], nb = 0, crt[kMaxBuckets], ncrt = 0;
     for (int cls = num_classes() - 1; cls >= 0; --cls)
