@@ -278,7 +278,8 @@ __device__ __forceinline__ void mont_setup(uint32_t (&one)[S / G], uint32_t (&r2
     if constexpr (B < 32) {
         const double rn = 1.0 / rgrp_scaled<S, G, B>(n, 0u, (int)bl);
         uint32_t left = nup;
-        auto move = [&]() {
+#pragma unroll
+        for (int step = 0; step < 2; ++step) {
             const uint32_t c = left < B - 1 ? left : (uint32_t)(B - 1);
             uint32_t y[L];
 #pragma unroll
@@ -287,12 +288,19 @@ __device__ __forceinline__ void mont_setup(uint32_t (&one)[S / G], uint32_t (&r2
 #pragma unroll
             for (int k = 0; k < L; ++k) one[k] = c ? y[k] : one[k];
             left -= c;
-        };
-#pragma unroll
-        for (int step = 0; step < 2; ++step) move();
+        }
         if constexpr (MOVES) {
 #pragma unroll 1
-            while (wave_max(left) > 6u) move();
+            while (wave_max(left) > 6u) {
+                const uint32_t c = left < B - 1 ? left : (uint32_t)(B - 1);
+                uint32_t y[L];
+#pragma unroll
+                for (int k = 0; k < L; ++k) y[k] = one[k];
+                rgrp_shl_mod<S, G, B>(y, c ? c : 1u, n, rn, (int)bl);
+#pragma unroll
+                for (int k = 0; k < L; ++k) one[k] = c ? y[k] : one[k];
+                left -= c;
+            }
         }
         const uint32_t maxd = wave_max(left);
         for (uint32_t t = 0; t < maxd; ++t) {
