@@ -239,12 +239,19 @@ static rns_exp_launcher rns_exp_of(const Resolved &r, size_t count, int cus)
 
 // Slots of the processing order of an RNS call: the tiles of both halves may
 // grow to the next number at which their launch changes shape (one tile per
-// CU, two, or a multiple of four), so that each key's run can start a tile of
-// its own; never more than the padded runs can take.
-static size_t rns_order_slots(size_t count, int cus)
+// CU, or two) or takes another round (of four tiles per CU, two of halves of
+// 48 words, one of 64), so that each key's run can start a tile of its own;
+// never more than the padded runs can take.  A round more costs more than
+// tiles of two keys (6144 messages of 60 4096-bit keys, 768 tiles: 8490 us
+// rounded to four rounds, 7200 in three with keys sharing tiles; 12000 of 60
+// 3072-bit keys, 1500 tiles: 6700 and 5720).
+static size_t rns_order_slots(const Resolved &r, size_t count, int cus)
 {
     const size_t cu = (size_t)cus, tiles = (count + kRnsTile - 1) / kRnsTile, both = 2 * tiles;
-    const size_t up = both <= cu ? cu : both <= 2 * cu ? 2 * cu : (both + 4 * cu - 1) / (4 * cu) * (4 * cu);
+    const size_t resident = (kClasses[r.cls] > 48 ? 1 : kClasses[r.cls] > 32 ? 2 : 4) * cu;
+    const size_t up = both <= cu                        ? cu
+                      : both <= 2 * cu && resident > cu ? 2 * cu
+                                                        : (both + resident - 1) / resident * resident;
     const size_t fit = up / 2 > tiles ? up / 2 : tiles, most = tiles + count;
     return (fit < most ? fit : most) * kRnsTile;
 }
@@ -400,7 +407,7 @@ extern "C" int rsa_decrypt_crt_batch(const uint32_t *c, const uint32_t *p, const
     size_t slots = count;
     const unsigned *order = nullptr;
     if (count > ng) {
-        slots = rns ? rns_order_slots(count, cus) : key_order_slots(count, ng, (size_t)cus);
+        slots = rns ? rns_order_slots(r, count, cus) : key_order_slots(count, ng, (size_t)cus);
         order = key_order(p, dp, dq, count, limbs / 2, ng, slots, stream);
         if (!order) slots = count;
     }
@@ -431,7 +438,7 @@ extern "C" int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p
     size_t slots = count;
     const unsigned *order = nullptr;
     if (count > ng) {
-        const size_t want = rns ? rns_order_slots(count, cus) : key_order_slots(count, ng, (size_t)cus);
+        const size_t want = rns ? rns_order_slots(r, count, cus) : key_order_slots(count, ng, (size_t)cus);
         slots = want < kStaticOrderMax ? want : kStaticOrderMax;    // >= count
         if (!(order = key_order_static(p, dp, dq, count, limbs / 2, ng, slots, stream))) return RSA_EHIP;
     }
