@@ -16,9 +16,11 @@
 // of radix_bn.hpp grows with the square of the width).
 //
 // Values are bounded, never reduced: residues are signed 32-bit words below
-// 0.9 * 2^31 (those in A below 0.73 m).  q carries a multiple of A (its extension is not
-// corrected), so |r| <= |x y| / A + 0.73 k n < 0.75 k n for inputs of that
-// size (rns_tables.py checks A and B against it).  The extension back is
+// 0.9 * 2^31 (those in A below 0.73 m; those of an entering x, whose limbs are
+// converted in sums of 7, below 0.94 * 2^31 in A).  q carries a multiple of A
+// (its extension is not corrected): its residues are below 0.86 m where both
+// factors have just entered, less otherwise, so |r| <= |x y| / A + 0.86 k n <
+// 0.875 k n (rns_tables.py checks A and B against it).  The extension back is
 // exact: alpha = round(sum_j xi_j / b_j) comes from the sum of the residues'
 // top digits (off by at most k / 256 < 0.3 + |r| / B), and -alpha B is one
 // more term of the matrix product.

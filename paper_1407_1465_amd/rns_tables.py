@@ -88,11 +88,11 @@ class Config:
         ps = primes_below_2_31(2 * k)
         a, b = self.a, self.b = ps[:k], ps[k:]
         self.A, self.B = math.prod(a), math.prod(b)
-        # values stay within +-0.75 k n (see csrc/rns_arith.hpp): the square
+        # values stay within +-0.875 k n (see csrc/rns_arith.hpp): the square
         # of that must vanish against A n, and it must be small against B
-        lim = (3 * k // 4 + 1) << bits
-        assert (3 * k // 4 + 1) ** 2 << bits < self.A >> 2 and lim < self.B >> 6
-        assert 128 << bits <= 1 << (LIMB_BITS * limbs) and 3 * k // 4 + 1 <= 64
+        lim = (7 * k // 8 + 1) << bits
+        assert (7 * k // 8 + 1) ** 2 << bits < self.A >> 2 and lim < self.B >> 6
+        assert 128 << bits <= 1 << (LIMB_BITS * limbs) and 7 * k // 8 + 1 <= 64
         self.w = [pow(self.B // p, -1, p) for p in b]
         self.ksteps = -(-units // 4)
         self._check_accumulators()
