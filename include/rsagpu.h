@@ -140,7 +140,7 @@ int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p, const uin
  * positional kernel is the faster one, and rsa_modexp_batch of 49 to 64 words
  * above 16 elements per compute unit (4096 on 256), where calls of public
  * exponents, which the host cannot tell apart, would pay for it (2048-bit
- * private exponents: 4096 take 2.2 ms in one call, 4097 take 14.2 ms, so larger
+ * private exponents: 4096 take 2.1 ms in one call, 4097 take 13.8 ms, so larger
  * batches of them go faster in calls of 4096).  Exponents of at most 64 bits,
  * encryptions and
  * every other width run on the positional kernels, which the plans below
@@ -166,7 +166,7 @@ int rsa_decrypt_crt_batch_static(const uint32_t *c, const uint32_t *p, const uin
  * operations inside rsa_ops_batch (separate plans: its buckets are smaller
  * and run side by side), 4 = the CRT half of the widest class of an
  * rsa_ops_batch call with at least 16384 operations (the bucket that ends
- * such a batch).
+ * such a batch on positional kernels).
  * Inputs and outputs are 32-bit limbs whatever the radix.  Pure host query.
  */
 typedef struct {
@@ -260,7 +260,8 @@ int rsa_init(void);
  * descriptors over keys of any sizes, run by one call: the operations are
  * sorted on the device into buckets of one width class and kind, and each
  * bucket is served by a persistent kernel whose waves claim operations from
- * an atomic counter until the bucket is empty (largest classes first).
+ * an atomic counter until the bucket is empty, or, where CRT halves run in
+ * RNS, by kernels over tiles of 16 of them (largest classes first).
  */
 typedef struct rsa_keyset rsa_keyset;
 

@@ -10,7 +10,8 @@
 // added, so an operation starts directly with its exponentiation.
 //
 // Operations are grouped on the device into buckets of one (width class,
-// kind), each ordered by key; each bucket is served by a persistent kernel
+// kind), each ordered by key; each bucket that does not run in RNS
+// (rns_io.hpp) is served by a persistent kernel
 // whose workgroups claim a chunk of operations at a time from an atomic
 // counter until the bucket is empty.
 #pragma once

@@ -69,12 +69,15 @@ struct Plan {
     int w;
 };
 //
+// What follows on CRT halves of 16 to 64 words is of their positional kernels,
+// which run where RNS does not (kPositional).
 // Kinds 2 and 3 are the same operations inside rsa_ops_batch, whose buckets
 // are usually far smaller than a plain batch and run side by side: there a
 // narrower group (more waves per operation) and a smaller LDS footprint (room
 // for the other buckets' waves) pay off.  Kind 4 is the CRT half of the
 // widest class of a bulk ops batch (rsa_ops_batch with at least
-// kBulkOps operations), whose end waits for that bucket's last operations.
+// kBulkOps operations), which ends with that bucket's last operations where
+// its buckets run positionally.
 // For 4096-bit keys kind 3 takes 16 lanes (S = 80): one operation's chain is
 // ~1.6x shorter than on 8 lanes for ~1.2x the lane-instructions, and a
 // serving batch ends with its 4096-bit decryptions (p99 50 -> 34 ms against
@@ -224,10 +227,13 @@ static rns_crt_launcher rns_crt_of(const Resolved &r, size_t count, int cus)
 // those of calls with short exponents, which the call cannot know: their RNS
 // kernel only finds that it has nothing to do.  To 16 words: one tile per SIMD
 // (32768 512-bit exponentiations in 692 us against 670 positionally, at 3 us
-// more for short exponents).  64 words: one tile per CU (8192 2048-bit
-// exponentiations 4731 us against 16532, but 16384 encryptions 191 against
-// 178).  In between any number: 16384 of 1536 bits 4130 us against 9567, short
-// ones 157 against 154; 65536 of 1024 bits 4333 against 6921.
+// more for short exponents).  64 words: one tile per CU (one key's private
+// exponent, 8192 elements 4284 us against 13758, but encryptions 161 against
+// 151, 16384 of them 175 against 157; with k_rns_pow on one looping workgroup a
+// CU 4638, 163 and 173).  In between any number: 16384 of 1536 bits 4130 us
+// against 9567, 65536 of 1024 bits 4333 against 6921; e = 65537, 4096 and 16384
+// elements, 24 words 37 and 47 us against 43 and 47, 32 words 58 and 63 against
+// 95 and 99, 48 words 87 and 132 against 94 and 141.
 static rns_exp_launcher rns_exp_of(const Resolved &r, size_t count, int cus)
 {
     if (!r.rns) return nullptr;
