@@ -237,12 +237,12 @@ def measured_peak(quick: bool = True):
 def timed(fn, steps, warmup, torch, per_step=None):
     """Mean ms per step over `steps` back-to-back steps (HIP events on the
     launch stream); per_step, if a list, receives each step's ms.  Python's
-    collector runs before, not within (a full collection took 36 ms of the
-    host between two of the encryptions' 0.18 ms launches)."""
-    for _ in range(warmup):
-        fn()
+    collector runs before the warm-up, not within (a full collection took 36
+    ms of the host between two of the encryptions' 0.18 ms launches)."""
     gc.collect()
     gc.disable()
+    for _ in range(warmup):
+        fn()
     torch.cuda.synchronize()
     stream = torch.cuda.current_stream()
     evs = [torch.cuda.Event(enable_timing=True) for _ in range(steps + 1)]
@@ -885,11 +885,14 @@ def main():
         # the decryptions' base extensions where their buckets run in RNS
         # (encryptions and the ways in and out are positional)
         crt = [(k, 4 if wl.keys[k].limbs == widest else 3) for kd, k in pairs if kd]
-        if all(rsagpu.get_path(wl.keys[k].limbs // 2, pk, nops) == rsagpu.PATH_RNS for k, pk in set(crt)):
-            ops8 = per_key_sum([k for k, _ in crt], lambda k: sum(
+        in_rns = {kp for kp in set(crt) if rsagpu.get_path(wl.keys[kp[0]].limbs // 2, kp[1], nops) == rsagpu.PATH_RNS}
+        if in_rns:
+            ops8 = per_key_sum([k for k, pk in crt if (k, pk) in in_rns], lambda k: sum(
                 rns_ops(d, wl.keys[k].limbs // 2, rns_window(wl.keys[k].limbs // 2, 0, cus, bulk=True))
                 for d in (wl.keys[k].dp, wl.keys[k].dq)))
-            line["roofline"] = rns_roofline(ops8, ms, nops, products, "k_rns_pow, k_ops_enc (all buckets)")
+            line["roofline"] = rns_roofline(ops8, ms, nops, products, "k_rns_pow and k_ops_* (all buckets)")
+            line["roofline"]["note"] = "%d of %d decryptions in RNS; the rest of the batch is positional" % (
+                sum(kp in in_rns for kp in crt), len(crt))
         else:
             line["roofline"] = roofline(products, ms, "k_ops_* (all buckets)", "per operation by size and kind",
                                         nops, as_run, measured_peak())
