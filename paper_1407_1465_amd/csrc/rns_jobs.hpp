@@ -131,7 +131,12 @@ struct RnsOpsSource {
         j.n = second ? k.q : k.p;
         j.e = second ? k.dq : k.dp;
         j.words = k.hwords;
-        j.io = mid + (size_t)o * kMidWords + (second ? 0 : k.hwords);
+        // opaque: recomputed from the operation's number, the way out's address
+        // cost the products' loop 1 to 2% (3000 2048-bit decryptions 1336 -> 1365
+        // us; again 1332)
+        unsigned long long off = (unsigned long long)o * kMidWords;
+        asm volatile("" : "+v"(off));
+        j.io = mid + off + (second ? 0 : k.hwords);
         return j;
     }
 };
