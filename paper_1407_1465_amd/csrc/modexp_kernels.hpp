@@ -637,13 +637,20 @@ __device__ __forceinline__ void from_mont(uint32_t (&A)[S / G], uint32_t *abuf, 
 // ---- out[i] = base[i]^exp[i] mod mod[i] --------------------------------
 //
 // S limbs of radix 2^B hold the caller's `limbs` 32-bit words (B*S >= 32*limbs).
-// With the registers capped (PIN) the compiler spills; n and x held in
-// registers across the set-up keep the spills out of the exponentiation's
-// loop, and n's vector loads pay.  64 words, 8192 elements, against vector
-// loads of both and no pin, us: one 2048-bit exponent 14107 -> 13694, an exponent
-// each 16857 -> 16844, e = 65537 153 -> 151 (16384: 160 -> 156).  Elsewhere
-// vector loads cost the loop up to 2% (96 words 15964 -> 16114, against 15768
-// by words) and bring a public exponent nothing.
+// How n and x load (by vectors or by words) and whether both are held in
+// registers across the set-up (PIN) decides what the compiler makes of the
+// exponentiation's loop, 2 to 5% of it, so each kind of group takes the
+// combination that measured best (us; vectors of both and no pin first):
+//   registers capped (14 or more limbs per lane), where it spills: n by
+//   vectors, x by words, pinned.  64 words, 8192 elements: one 2048-bit
+//   exponent 14107 -> 13694, one each 16857 -> 16844, e = 65537 153 -> 151;
+//   2 lanes: vectors of both, pinned.  16 words, 16385 elements: 624 -> 618,
+//   one each 851 -> 852, 20000 with e = 65537 37.0 -> 36.9 (by words 636, 834,
+//   39.5);
+//   4 lanes: words.  24 words, 2000 elements: 1170 -> 1135;
+//   8 and 16 lanes: n by words, x by vectors.  48 words, 2000 elements: 5535 ->
+//   5324, one each 5826 -> 5569; 96 words 16044 -> 15802; 128 words 32689 ->
+//   32545.
 template <int S, int G, int B>
 __global__ __launch_bounds__(64) RSAGPU_EXP_OCC(S / G) void k_modexp(const uint32_t *__restrict__ base,
                                                const uint32_t *__restrict__ exp,
@@ -653,7 +660,7 @@ __global__ __launch_bounds__(64) RSAGPU_EXP_OCC(S / G) void k_modexp(const uint3
 {
     using Ar = Arith<S, G, B>;
     constexpr int L = S / G, NG = 64 / G;
-    constexpr bool PIN = B < 32 && exp_waves_per_simd<L>() > 1;
+    constexpr bool CAPPED = exp_waves_per_simd<L>() > 1, PIN = B < 32 && (CAPPED || G == 2);
     uint32_t *lds = reinterpret_cast<uint32_t *>(rsagpu_lds);
     const int g = grp_index<G>(), r = grp_lane<G>();
     const unsigned long long msg = (unsigned long long)blockIdx.x * NG + g;
@@ -661,9 +668,10 @@ __global__ __launch_bounds__(64) RSAGPU_EXP_OCC(S / G) void k_modexp(const uint3
     const size_t off = live ? (size_t)msg * (size_t)limbs : 0;
 
     uint32_t n[L], x[L];
-    if constexpr (PIN) Ar::load(n, mod + off, limbs, 0, live);
+    if constexpr (CAPPED || G == 2) Ar::load(n, mod + off, limbs, 0, live);
     else Ar::load_words(n, mod + off, limbs, 0, live);
-    Ar::load_words(x, base + off, limbs, 0, live);
+    if constexpr (!CAPPED && G != 4) Ar::load(x, base + off, limbs, 0, live);
+    else Ar::load_words(x, base + off, limbs, 0, live);
     const uint32_t n0 = grp_bcast0<G>(n[0]);
     const uint32_t bl = Ar::bitlen(n);
     const bool valid = live && (n0 & 1u) && bl > 1;
